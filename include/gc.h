@@ -210,7 +210,10 @@ enum gc_algorithm {
                         neighbours in the first round in which all of them are
                         coloured.  The colours equal the sequential ones bit for
                         bit; R is the number of vertices on the longest path
-                        whose ids increase                                      */
+                        whose ids increase.  The default driver runs them as
+                        one data-flow pass (4 or 8 bytes per vertex of device
+                        memory, and 4 per 64 vertices); a round cap or another
+                        mode runs a pass per round                             */
   GC_ALGO_BLOCKS = 4 /* Algorithm 1 of Section 3.1 read literally with p =
                         GC_OPT_PARTITIONS blocks of consecutive ids: every
                         vertex keeps a ForbiddenColors slot per neighbour; in
@@ -235,7 +238,9 @@ int gc_get_option(gc_handle h, int option, int64_t *value);
 /*
  * gc_get_profile -- kernel times accumulated over profiled calls
  * (GC_OPT_PROFILE = 1), per kernel kind: [0] round 1, [1] speculate,
- * [2] detect/commit, [3] finish (colour count and widening).  `ms` (4
+ * [2] detect/commit, [3] finish (colour count and widening).  A data-flow
+ * pass (GC_ALGO_SEQ) counts as one speculate, the clearing before it as
+ * round 1.  `ms` (4
  * doubles) receives total milliseconds, `launches` (4 int64) the launch
  * counts; either may be NULL.  Speculate and detect are timed once the round
  * count is known (calls still discovering R, and persistent calls, add only

@@ -124,6 +124,14 @@ struct gc_ctx {
   int32_t* bslot = nullptr;  // device, nnz: ForbiddenColors slots (GC_ALGO_BLOCKS)
   uint8_t* btodo = nullptr;  // device, n
 
+  // data-flow pass of GC_ALGO_SEQ, allocated on first use
+  void* word = nullptr;         // device, n words
+  int word_bytes = 0;
+  int32_t* starts = nullptr;    // device: units of the current degree classes (launch_flow_units)
+  int64_t starts_room = 0;
+  int32_t* unit_part = nullptr; // device, kUnitGrid + 1: per-workgroup unit counts, the number of units
+  bool units_ready = false;
+
   Captured chunk;  // discovery chunk (chunk_rounds)
   Captured exact;  // R - 1 rounds, once R is known
 
@@ -269,6 +277,7 @@ static int classify(gc_ctx* h, hipStream_t s) {
   h->mcount = h->host->counts[0];
   h->hcount = h->host->counts[1];
   h->maxdeg = h->host->counts[2];
+  h->units_ready = false;
   LCHECK(h, gc::launch_wide_index(h->hlist, h->hcount, h->mcount, h->widx, s));
   h->lists_dirty = false;
   return GC_OK;
@@ -308,6 +317,9 @@ static void free_ctx(gc_ctx* h) {
   if (h->o_colors) (void)hipFree(h->o_colors);
   if (h->bslot) (void)hipFree(h->bslot);
   if (h->btodo) (void)hipFree(h->btodo);
+  if (h->word) (void)hipFree(h->word);
+  if (h->starts) (void)hipFree(h->starts);
+  if (h->unit_part) (void)hipFree(h->unit_part);
   if (h->host) (void)hipHostFree(h->host);
   delete h;
 }
@@ -627,6 +639,93 @@ static int color_blocks(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipSt
   return rc;
 }
 
+// Bits that hold 0..x.
+static int bits_of(int64_t x) {
+  int b = 1;
+  while (b < 63 && (x >> b) != 0) ++b;
+  return b;
+}
+
+// Sequential First Fit in one data-flow pass (default driver of GC_ALGO_SEQ;
+// a round cap and the explicit drivers keep the launch per round).
+static int color_flow(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStream_t s) {
+  gc::FlowArgs f{};
+  f.rowptr = h->rowptr;
+  f.colidx = h->colidx;
+  f.colors = colors_out;
+  f.n = (int32_t)h->n;
+  f.light_max = light_max_of(h, auto_lanes(h));
+  f.sorted = (h->flags & GC_ROWS_SORTED) != 0;
+  // colours never exceed the degree, rounds never n
+  f.cbits = bits_of(h->maxdeg);
+  f.wide = f.cbits + bits_of(h->n) > 32;
+  if (f.wide) f.cbits = 32;
+  f.ctrl = h->ctrl;
+  const int wb = f.wide ? 8 : 4;
+  const int64_t room = (h->n + gc::kWave - 1) / gc::kWave + 2 * ((int64_t)h->mcount + h->hcount) + 1;
+  if (wb > h->word_bytes || room > h->starts_room || !h->unit_part) {
+    int rc = ensure_idle(h);
+    if (rc) return rc;
+    for (void* p : {h->word, (void*)h->starts, (void*)h->unit_part})
+      if (p) (void)hipFree(p);
+    h->word = nullptr;
+    h->starts = h->unit_part = nullptr;
+    h->word_bytes = 0;
+    h->starts_room = 0;
+    h->units_ready = false;
+    hipError_t e = hipMalloc(&h->word, (size_t)h->n * wb);
+    if (e == hipSuccess) e = hipMalloc((void**)&h->starts, (size_t)room * sizeof(int32_t));
+    if (e == hipSuccess)
+      e = hipMalloc((void**)&h->unit_part, (gc::kUnitGrid + 1) * sizeof(int32_t));
+    if (e != hipSuccess) return set_err(h, GC_ENOMEM, "data-flow words: %s", hipGetErrorString(e));
+    h->word_bytes = wb;
+    h->starts_room = room;
+  }
+  f.word = h->word;
+  f.starts = h->starts;
+  f.units = h->unit_part + gc::kUnitGrid;
+  if (!h->units_ready) {
+    LCHECK(h, gc::launch_flow_units(f, h->rp64, h->unit_part, h->starts,
+                                    h->unit_part + gc::kUnitGrid, gc::kUnitGrid, s));
+    h->units_ready = true;
+  }
+  h->stats_ready = false;
+  KArgs a = make_args(h, colors_out, f.light_max);
+  a.clear_trace = 1;  // the finishing pass adds the round sizes into the trace
+  // Two workgroups per CU: more only widen the window of ids in flight, whose
+  // vertices poll without being able to finish (uniform random graph, 2^24
+  // edges: 331 us at two, 340 at one, 421 at three, over 600 at eight).
+  const int grid = (int)std::max<int64_t>(
+      1, std::min<int64_t>((int64_t)h->cus * 2, (room + gc::kWavesPerBlock - 1) / gc::kWavesPerBlock));
+  if (h->profile) {  // the clearing pass as round 1, the data-flow pass as one speculate
+    int rc = reserve_round_events(h, 1);
+    if (rc) return rc;
+  }
+  LCHECK(h, gc::launch_init(a, s));
+  if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[0], s));
+  LCHECK(h, gc::launch_flow_clear(f, round_grid(h), s));
+  if (h->profile) {
+    HIPCHECK(h, hipEventRecord(h->pev[1], s));
+    HIPCHECK(h, hipEventRecord(h->rev[0], s));
+  }
+  LCHECK(h, gc::launch_flow(f, h->rp64, grid, s));
+  if (h->profile) {
+    HIPCHECK(h, hipEventRecord(h->rev[1], s));
+    HIPCHECK(h, hipEventRecord(h->rev[2], s));
+    h->timed_rounds = 1;
+    HIPCHECK(h, hipEventRecord(h->pev[2], s));
+  }
+  LCHECK(h, gc::launch_flow_finish(f, h->fin_dev, s));
+  if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[3], s));
+  h->pending_profile = h->profile;
+  int rc = permute_back(h, colors_out, user_out, s);
+  if (rc) return rc;
+  HIPCHECK(h, hipEventRecord(h->done, s));
+  h->in_flight = true;
+  h->stats_ready = true;
+  return GC_OK;
+}
+
 extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   if (!h) return set_err(nullptr, GC_EINVAL, "gc_color: NULL handle");
   if (h->n > 0 && !colors_out) return set_err(h, GC_EINVAL, "gc_color: colors_out is NULL");
@@ -656,6 +755,8 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   }
   (void)hipGetLastError();  // launch checks below must see only this call's errors
   if (h->algorithm == GC_ALGO_BLOCKS) return color_blocks(h, colors_out, user_out, s);
+  if (use_seq(h) && h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH)
+    return color_flow(h, colors_out, user_out, s);
   if (use_push(h)) {
     if (!h->seen && h->n > 0) {
       const size_t nv = (size_t)(h->n + gc::kWave - 1) / gc::kWave * gc::kWave;  // whole chunks
@@ -818,7 +919,7 @@ static int wait_done(gc_ctx* h) {
   }
   fold_finish(h);  // the call has completed (also when another path waited for it)
   collect_profile(h);
-  if (h->host->abort) return set_err(h, GC_EDEVICE, "persistent kernel: grid barrier timed out");
+  if (h->host->abort) return set_err(h, GC_EDEVICE, "a wait inside a kernel timed out");
   if (h->host->left) {
     if (h->max_rounds > 0 && h->host->last_round >= h->max_rounds)
       return set_err(h, GC_EROUNDS, "round cap reached with %d vertices uncoloured", h->host->left);

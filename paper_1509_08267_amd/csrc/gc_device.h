@@ -55,6 +55,10 @@ __device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {
   return pos;
 }
 
+__device__ __forceinline__ void store_system(int32_t* p, int32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // tentative colour carried by a state word (final colours decode to themselves)
 __device__ __forceinline__ int tent_of(int s) { return s < 0 ? ~s : s; }
 

@@ -64,6 +64,8 @@ struct Ctrl {
   Line pend;             // round whose per-workgroup counts in KArgs::part are not yet in
                          // trace (0: none)
   Line pend_grid;        // workgroups of that round's detect pass
+  Line ticket;           // next unit of the data-flow pass (GC_ALGO_SEQ)
+  Line over;             // its vertices of a round beyond the trace
   Line tasks;            // 64-bit: push tasks (high half) and their pieces (low half)
                          // queued by this round's detect pass (KArgs::tasks)
   int32_t trace[kTraceRounds];  // |U_r| at slot r - 1
@@ -126,6 +128,33 @@ struct KArgs {
                           // kernel; null otherwise)
   Ctrl* ctrl;
 };
+
+// Arguments of the data-flow pass of the id-priority schedule (gc_seq.hip).
+struct FlowArgs {
+  const void* rowptr;     // int32 or int64, n + 1
+  const int32_t* colidx;  // nnz
+  void* word;             // n words, uint32 or (wide) uint64: 0, or (round << cbits) | colour
+  int32_t* colors;        // n, the caller's output
+  int32_t n;
+  int32_t light_max;      // deg <= light_max: a lane per vertex, above: a wavefront
+  int32_t sorted;         // rows ascending: a row is read up to its first id above the vertex
+  int32_t wide;           // 64-bit words (cbits = 32): colours and rounds don't fit 32 bits together
+  int32_t cbits;          // bits of a colour (at most the maximum degree) in a word
+  const int32_t* starts;  // first id of each unit, and n behind the last
+  const int32_t* units;   // their number
+  Ctrl* ctrl;
+};
+constexpr int kUnitGrid = 256;  // workgroups of the passes that build the units
+
+// The units for `a`'s graph and light_max: their first ids into `starts`
+// (room for one per 64 vertices and two per vertex of degree above light_max,
+// and one), their number into `units`; `part` holds kUnitGrid words.
+int launch_flow_units(const FlowArgs& a, bool rp64, int32_t* part, int32_t* starts, int32_t* units,
+                      int grid, void* stream);
+int launch_flow_clear(const FlowArgs& a, int grid, void* stream);
+int launch_flow(const FlowArgs& a, bool rp64, int grid, void* stream);
+// Writes the caller's colours, the trace and `out` (as launch_finish).
+int launch_flow_finish(const FlowArgs& a, int32_t* out, void* stream);
 
 // Arguments of the p-block kernels (GC_ALGO_BLOCKS, gc_blocks.hip).
 struct BArgs {

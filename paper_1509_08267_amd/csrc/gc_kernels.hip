@@ -1006,7 +1006,7 @@ __global__ void k_init(KArgs a) {
   const long tid = blockIdx.x * (long)blockDim.x + threadIdx.x;
   const long nth = (long)gridDim.x * blockDim.x;
   // round sizes: every round the colouring runs stores its own; only the
-  // p-block passes add into them
+  // p-block passes and the data-flow pass add into them
   if (a.clear_trace)
     for (long i = tid; i < kTraceRounds; i += nth) a.ctrl->trace[i] = 0;
   if (a.push && a.clear_seen) {
@@ -1033,6 +1033,8 @@ __global__ void k_init(KArgs a) {
     a.ctrl->bar.v = 0;
     a.ctrl->abort.v = 0;
     a.ctrl->left.v = 0;
+    a.ctrl->ticket.v = 0;
+    a.ctrl->over.v = 0;
     *(uint64_t*)&a.ctrl->tasks = 0;
     a.ctrl->epoch.v = a.epoch;
   }
@@ -1040,10 +1042,6 @@ __global__ void k_init(KArgs a) {
 
 __global__ void k_advance_base(Ctrl* c, int by) {
   if (threadIdx.x == 0 && blockIdx.x == 0) c->round_base.v += by;
-}
-
-__device__ __forceinline__ void store_system(int32_t* p, int32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Widening pass and statistics: the state becomes the caller's int32
