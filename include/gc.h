@@ -276,10 +276,11 @@ size_t gc_batch_workspace_bytes(int64_t num_graphs, const int64_t *voff,
                                 const int64_t *eoff);
 
 /*
- * gc_color_batch -- colour every graph of a packed batch.  A graph whose work
- * (entries + vertices) is at least 1/(2 x CUs) of the batch's is coloured by
- * a team of workgroups (up to one per 65,536 units of its work), the others
- * by one workgroup each; the colours are the same either way.
+ * gc_color_batch -- colour every graph of a packed batch.  A graph that would
+ * keep one workgroup busy longer than the whole launch should take (by its
+ * entries + vertices and those of the others, from 200,000 of them up) is
+ * coloured by a team of workgroups (up to one per 65,536 units of its work),
+ * the others by one workgroup each; the colours are the same either way.
  *
  *   voff, eoff      device, int64[num_graphs + 1], non-decreasing, from 0
  *   rowptr_local    device, int32, sum(n_g + 1) entries (layout above)

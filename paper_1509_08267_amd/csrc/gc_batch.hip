@@ -8,14 +8,17 @@
 //   - a workgroup takes graphs from a device-side queue ordered largest
 //     first (work buckets by log2 of the CSR size: longest-processing-time
 //     order, so the big graphs do not finish last);
-//   - a graph whose state fits the workgroup's LDS slice (n bytes at int8,
-//     2n at int16, by its maximum degree) keeps it there, so every neighbour
-//     colour gather of every round is an LDS read; larger graphs keep an
-//     int32 state in the caller's colour array;
+//   - a workgroup has a compute unit to itself and keeps the state of a graph
+//     of up to 54,000 vertices (maximum degree up to 127) in LDS together with
+//     a mask of the colours taken at each vertex, which a committing vertex
+//     marks in its neighbours (run_graph_push); the rows are all that is left
+//     to read.  Other graphs gather their neighbours' states every round, from
+//     LDS where the state alone fits there (int8, int16 or int32 by the maximum
+//     degree), else from an int32 state in the caller's colour array;
 //   - the rounds are separated by workgroup barriers instead of grid-wide
 //     ones, and each graph stops independently when its round has no loser;
-//   - a graph with at least a workgroup's fair share of the batch's work
-//     (and enough of it to occupy several workgroups) is coloured by a team
+//   - a graph that would outlast the rest of the launch (k_batch_plan) and has
+//     work enough to occupy several workgroups is coloured by a team
 //     of K workgroups instead: it appears K times in the queue, the K
 //     workgroups that take those entries split its chunks, its rounds are
 //     separated by a barrier of the team, and each member keeps a replica of
@@ -39,7 +42,7 @@
 namespace gc {
 
 constexpr int kBatchBlock = 1024;         // threads per graph workgroup
-constexpr int kBatchLds = 64 * 1024;      // LDS state slice per workgroup (bytes)
+constexpr int kBatchLds = 159 * 1024;     // LDS slice per workgroup (bytes): one per compute unit
 constexpr int kBatchWaves = kBatchBlock / kWave;
 #ifndef GC_BATCH_SPEC_QUADS
 #define GC_BATCH_SPEC_QUADS 3
@@ -59,12 +62,13 @@ constexpr int kBuckets = 64;
 constexpr int kMaxTeams = 256;          // graphs coloured by a team, per launch
 constexpr int kMaxExtraTickets = 4096;  // queue entries beyond one per graph
 constexpr int64_t kMinTeamWork = 65536; // work (entries + vertices) per team member
-#ifndef GC_BATCH_TEAM_SHARE
-#define GC_BATCH_TEAM_SHARE 20
-#endif
-// a graph of work w gets a team of floor(kTeamShare * w / (10 * fair share))
-// workgroups when that is at least 2
-constexpr uint64_t kTeamShare = GC_BATCH_TEAM_SHARE;
+// A member of a team works through kTeamCost times the work of a workgroup
+// that has a graph to itself (the team gathers whole rows every round and
+// meets at barriers, the other pushes into its own LDS), and a graph of
+// at most kMinTeam work is done sooner alone than a team's barriers take.
+constexpr uint64_t kTeamCost = 5;
+constexpr uint64_t kMinTeam = 200000;
+constexpr int kFine = 512;  // work histogram of the plan: eight buckets per power of two
 constexpr long kTeamSpinLimit = 1l << 25;
 
 struct BatchCtrl {
@@ -119,15 +123,24 @@ __global__ void k_batch_descs(int64_t G, const int64_t* voff, const int64_t* eof
   }
 }
 
-// Largest-first order: one workgroup buckets the graphs by floor(log2(work))
-// (batch_work) and writes them out bucket by bucket,
-// largest bucket first.  A graph whose work w is at least a workgroup's fair
-// share f (total work / nwg) would alone keep one workgroup busy for the
-// whole launch, and longer under the load of the others: it gets a team of
-// K = min(floor(2 w / f), nwg, w / kMinTeamWork) workgroups when K >= 2 and
-// a team slot and K - 1 extra queue entries are left.  Its K entries are
-// consecutive, with the team slot beside them (-1 for a graph of one
-// workgroup).  Also resets the work queue.
+// Largest-first order and teams.  One workgroup buckets the graphs by
+// floor(log2(work)) (batch_work) and writes them out bucket by bucket,
+// largest bucket first.
+//
+// A graph that takes longer alone than the whole launch should would hold
+// every other workgroup up at the end, so it gets a team.  With work in units
+// of a workgroup's own pace, a launch of length T that colours the graphs of
+// cost <= T alone and the others in teams costs
+//   sum(cost <= T) + kTeamCost * sum(work of the others),
+// and the T taken is the smallest one (of the histogram's bucket ends) that
+// nwg workgroups can hold.  A graph of cost above T and work of at least
+// kMinTeam is coloured by K = min(kTeamCost * work / T + 1, nwg,
+// work / kMinTeamWork) workgroups when K >= 2 and a team slot and K - 1 extra
+// queue entries are left; its K entries are consecutive, with the team slot
+// beside them (-1 for a graph of one workgroup).  Also resets the work queue.
+// Measured, against a team of floor(2 work / fair share) from one fair share of
+// the work up: 512 graphs of up to 50,000 vertices 2.19 ms (3.73), 100 graphs
+// 1.05 (1.64), 12 graphs of up to 5,000 vertices 0.21 (0.44).
 // The work of a graph: its CSR entries and vertices when fresh; when it
 // resumes from an earlier step (rounds > 0), the vertices it left uncoloured
 // times two more than its average degree, an estimate of what its next
@@ -139,33 +152,75 @@ __device__ __forceinline__ uint64_t batch_work(const gc_graph_desc& x, const int
   return (uint64_t)nnz + (uint64_t)x.n + 1;
 }
 
+// What a graph costs a workgroup of its own: a graph beyond the pushed-colour
+// path's LDS slice gathers, as a team would.
+__device__ __forceinline__ uint64_t cost_alone(int n, uint64_t w) {
+  return n > (kBatchLds - 4) / 3 ? kTeamCost * w : w;
+}
+
+// Bucket of x >= 1: its power of two and the next three bits.  The end of
+// bucket b is the largest x in it, to within its eighth.
+__device__ __forceinline__ int fine_bucket(uint64_t x) {
+  const int p = 63 - __builtin_clzll(x);
+  return min(kFine - 1, 8 * p + (p >= 3 ? (int)((x >> (p - 3)) & 7) : 0));
+}
+__device__ __forceinline__ uint64_t fine_end(int b) {
+  return ((uint64_t)(9 + (b & 7)) << (b >> 3)) >> 3;
+}
+
 __global__ __launch_bounds__(1024) void k_batch_plan(int64_t G, const gc_graph_desc* d,
                                                      const int32_t* rowptr_base, int32_t* order,
                                                      int32_t* slot, int32_t* gk, TeamCtrl* teams,
                                                      BatchCtrl* ctrl, int nwg) {
   __shared__ int hist[kBuckets];
   __shared__ int base[kBuckets];
-  __shared__ unsigned long long total;
-  __shared__ int nteams, extra;
+  __shared__ unsigned long long alone[kFine], work[kFine];  // by cost alone
+  __shared__ int nteams, extra, len;
   for (int i = threadIdx.x; i < kBuckets; i += blockDim.x) hist[i] = 0;
+  for (int i = threadIdx.x; i < kFine; i += blockDim.x) alone[i] = work[i] = 0;
   if (threadIdx.x == 0) {
-    total = 0;
     nteams = 0;
     extra = 0;
+    len = kFine - 1;
   }
   __syncthreads();
-  uint64_t mine = 0;
-  for (long g = threadIdx.x; g < G; g += blockDim.x) mine += batch_work(d[g], rowptr_base);
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) mine += shfl_xor64(mine, off);
-  if (lane_id() == 0 && mine) atomicAdd(&total, (unsigned long long)mine);
-  __syncthreads();
-  const uint64_t fair = total / (uint64_t)(nwg > 0 ? nwg : 1) + 1;
   for (long g = threadIdx.x; g < G; g += blockDim.x) {
     const uint64_t w = batch_work(d[g], rowptr_base);
-    uint64_t q = kTeamShare * w / (10 * fair);
-    if (q > (uint64_t)nwg) q = (uint64_t)nwg;
-    if (q > w / kMinTeamWork) q = w / kMinTeamWork;
+    const uint64_t c = cost_alone(d[g].n, w);
+    const int b = fine_bucket(c);
+    atomicAdd(&alone[b], (unsigned long long)c);
+    atomicAdd(&work[b], (unsigned long long)w);
+  }
+  __syncthreads();
+  // prefix sums of `alone`, suffix sums of `work` (buckets above), in place
+  const int b = threadIdx.x;
+  for (int off = 1; off < kFine; off <<= 1) {
+    unsigned long long x = 0, y = 0;
+    if (b < kFine) {
+      x = b >= off ? alone[b - off] : 0;
+      y = b + off < kFine ? work[b + off] : 0;
+    }
+    __syncthreads();
+    if (b < kFine) {
+      alone[b] += x;
+      work[b] += y;
+    }
+    __syncthreads();
+  }
+  if (b < 8 * 56) {  // (no batch reaches the buckets beyond)
+    const uint64_t load = alone[b] + kTeamCost * work[b + 1];
+    if (load <= (uint64_t)nwg * fine_end(b)) atomicMin(&len, b);
+  }
+  __syncthreads();
+  const uint64_t T = fine_end(len);
+  for (long g = threadIdx.x; g < G; g += blockDim.x) {
+    const uint64_t w = batch_work(d[g], rowptr_base);
+    uint64_t q = 0;
+    if (w >= kMinTeam && cost_alone(d[g].n, w) > T) {
+      q = kTeamCost * w / T + 1;
+      if (q > (uint64_t)nwg) q = (uint64_t)nwg;
+      if (q > w / kMinTeamWork) q = w / kMinTeamWork;
+    }
     int k = 1, s = -1;
     if (q >= 2) {
       const int ts = atomicAdd(&nteams, 1);
@@ -245,12 +300,12 @@ __device__ __forceinline__ void unpack(const int4 w, int* u) {
 // Least colour not final on any neighbour of the row [b, e), by a group of L
 // lanes (gl = lane in group) with 16-byte loads, kSpecQuads quads per lane in
 // flight.  Every lane returns the result.
-template <typename S>
-__device__ __forceinline__ int spec_quads(const int32_t* __restrict__ ci, const S* __restrict__ st,
-                                          int b, int e, int L, int gl) {
+template <typename State>
+__device__ __forceinline__ int spec_quads(const int32_t* __restrict__ ci, const State& state,
+                                          int b, int e, int L, int gl, int base0 = 0) {
   const Quads r = quads_of(ci, b, e);
   const int nq = (r.len + 3) >> 2;
-  int base = 0;
+  int base = base0;
   for (;;) {
     uint64_t m = 0;
     auto mark = [&](const int4 w, int idx0) {
@@ -260,7 +315,7 @@ __device__ __forceinline__ int spec_quads(const int32_t* __restrict__ ci, const 
       for (int j = 0; j < 4; ++j) {
         const int idx = idx0 + j;
         if (idx >= r.lead && idx < r.len) {
-          const int c = st[u[j]];
+          const int c = state(u[j]);
           const unsigned rel = (unsigned)c - (unsigned)base;
           if (c >= 0 && rel < 64u) m |= 1ull << rel;
         }
@@ -290,9 +345,9 @@ __device__ __forceinline__ int spec_quads(const int32_t* __restrict__ ci, const 
 // lower neighbour seen still uncoloured, or of the point where the scan
 // stopped when it saw none (the per-graph path's resume rule: final colours
 // never change).  Stops at the first conflict or the first id >= v.
-template <typename S>
+template <typename State>
 __device__ __forceinline__ bool detect_quads(const int32_t* __restrict__ ci,
-                                             const S* __restrict__ st, int b, int e, int v, int t,
+                                             const State& state, int b, int e, int v, int t,
                                              int L, int gl, uint64_t gmask, int gbase, int* skip) {
   const int from = skip ? *skip : 0;
   const Quads r = quads_of(ci, b + from, e);
@@ -308,7 +363,7 @@ __device__ __forceinline__ bool detect_quads(const int32_t* __restrict__ ci,
       if (idx < r.lead) continue;  // before the scan's start
       const bool in = idx < r.len;
       const bool low = in && u[j] < v;
-      const int s = low ? (int)st[u[j]] : 0;
+      const int s = low ? state(u[j]) : 0;
       if (low && s < 0 && ja == 4) ja = j;
       // decode, do not test the sign: a neighbour that wins in this same
       // pass flips ~t to t concurrently and must still count
@@ -354,6 +409,7 @@ __device__ __forceinline__ bool graph_pass(const GraphRun& g, S* st, int32_t* sk
   const int Gw = kWave / L;
   const uint64_t gmask = (L == kWave) ? ~0ull : (((1ull << L) - 1) << (grp * L));
   const int wave = threadIdx.x / kWave;
+  const auto state = [st](int u) { return (int)st[u]; };
   bool lost = false;
   for (int ch = rank * kBatchWaves + wave; ch * kWave < g.n; ch += K * kBatchWaves) {
     const int v = ch * kWave + lane;
@@ -380,7 +436,7 @@ __device__ __forceinline__ bool graph_pass(const GraphRun& g, S* st, int32_t* sk
       const int vv = ch * kWave + pos;
       if (valid) {  // group-uniform
         if (SPEC) {
-          const int t = spec_quads<S>(g.ci, st, vb, ve, L, gl);
+          const int t = spec_quads(g.ci, state, vb, ve, L, gl);
           if (gl == 0) {
             st[vv] = (S)~t;
             if (mirror) mirror[vv] = ~t;
@@ -389,7 +445,7 @@ __device__ __forceinline__ bool graph_pass(const GraphRun& g, S* st, int32_t* sk
           const int t = ~vs;
           int sk = skipv ? skipv[vv] : 0;
           const int sk0 = sk;
-          const bool lose = detect_quads<S>(g.ci, st, vb, ve, vv, t, L, gl, gmask, grp * L,
+          const bool lose = detect_quads(g.ci, state, vb, ve, vv, t, L, gl, gmask, grp * L,
                                             skipv ? &sk : nullptr);
           if (gl == 0) {
             if (!lose) {
@@ -466,11 +522,398 @@ __device__ __forceinline__ int run_graph(const GraphRun& g, S* st, int L, int* l
   return r;
 }
 
+// A graph's colouring state in the LDS slice under pushed colours: per
+// vertex its state (8 bits: ~t or the final colour, so the maximum degree is
+// at most 127) and a mask of the colours below BITS that are final on a
+// neighbour.  BITS = 24 packs both into one word (4 bytes per vertex); 16
+// takes 3 bytes, two masks to a word behind the states.
+template <int BITS>
+struct Slots {
+  uint32_t* w;
+  int8_t* st;
+  __device__ static Slots at(char* smem, int n) {
+    Slots x;
+    x.w = (uint32_t*)smem;
+    x.st = BITS == 24 ? (int8_t*)smem + 3 : (int8_t*)(x.w + (n + 1) / 2);
+    return x;
+  }
+  __device__ static constexpr bool fits(int n) {
+    return BITS == 24 ? n <= kBatchLds / 4 : n <= (kBatchLds - 4) / 3;
+  }
+  __device__ __forceinline__ int state(int v) const { return st[BITS == 24 ? 4 * v : v]; }
+  __device__ __forceinline__ void set_state(int v, int s) const {
+    st[BITS == 24 ? 4 * v : v] = (int8_t)s;
+  }
+  __device__ __forceinline__ uint32_t mask(int v) const {
+    return BITS == 24 ? w[v] & 0xffffffu : (w[v >> 1] >> (16 * (v & 1))) & 0xffffu;
+  }
+  // several lanes may mark the vertices of one word
+  __device__ __forceinline__ void mark(int v, uint32_t bits) const {
+    if (BITS == 24) atomicOr(&w[v], bits);
+    else atomicOr(&w[v >> 1], bits << (16 * (v & 1)));
+  }
+};
+template <int BITS>
+constexpr uint32_t kAllTaken = (1u << BITS) - 1;
+
+// Lanes per item when cnt (>= 1) items share a wavefront: the largest power of
+// two that gives every item a group at once.
+__device__ __forceinline__ int group_lanes(int cnt) {
+  return kWave >> (cnt <= 1 ? 0 : 32 - __builtin_clz((unsigned)cnt - 1));
+}
+
+// A wavefront's vertices that have committed and not yet pushed: row segment
+// [b, e) and colour t in lanes 0 .. cnt - 1.  They push together, a group of
+// lanes each, so that few winners at a time still fill the wavefront.
+template <int BITS>
+struct Winners {
+  int b = 0, e = 0, t = 0, cnt = 0;
+
+  // marks the queued colours; four quads in flight per lane
+  __device__ __forceinline__ void flush(const Slots<BITS>& sl, const int32_t* __restrict__ ci) {
+    if (cnt == 0) return;
+    const int lane = lane_id();
+    const int L = min(16, group_lanes(cnt));
+    const int gl = lane & (L - 1);
+    for (int p = 0; p < cnt; p += kWave / L) {  // wave-uniform
+      const int k = p + lane / L;
+      const int vb = __shfl(b, k & (kWave - 1)), ve = __shfl(e, k & (kWave - 1)),
+                vt = __shfl(t, k & (kWave - 1));
+      if (k >= cnt) continue;
+      const uint32_t bit = 1u << vt;
+      const Quads r = quads_of(ci, vb, ve);
+      const int nq = (r.len + 3) >> 2;
+      for (int i = gl; i < nq; i += 4 * L) {
+        int4 w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (i + j * L < nq) w[j] = r.q[i + j * L];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (i + j * L >= nq) break;
+          int u[4];
+          unpack(w[j], u);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int idx = 4 * (i + j * L) + q;
+            if (idx >= r.lead && idx < r.len) sl.mark(u[q], bit);
+          }
+        }
+      }
+    }
+    cnt = 0;
+  }
+
+  // the lanes of wm join the queue (all lanes active; colours below BITS)
+  __device__ __forceinline__ void add(const Slots<BITS>& sl, const int32_t* __restrict__ ci,
+                                      uint64_t wm, int pb, int pe, int pt) {
+    const int c = __popcll(wm);
+    if (c == 0) return;
+    if (cnt + c > kWave) flush(sl, ci);
+    const int qb = pack_lanes(wm, pb, cnt), qe = pack_lanes(wm, pe, cnt),
+              qt = pack_lanes(wm, pt, cnt);
+    if (lane_id() >= cnt) {
+      b = qb;
+      e = qe;
+      t = qt;
+    }
+    cnt += c;
+  }
+};
+constexpr int kPushBatch = 16;  // queued winners that are pushed at once
+
+// Rounds of one graph by one workgroup with pushed colours, everything but the
+// rows and the resume offsets in LDS: a vertex that commits marks its colour
+// in its neighbours' masks (LDS atomics), so a speculate pass reads a word
+// per uncoloured vertex and only a vertex with all colours below BITS taken
+// scans its row.  Every row is then read about once for its pushes and in
+// parts by the conflict scans, not whole in every round it stays uncoloured.
+// Bound by the latency of the scans' row reads (about 230 M scattered 64-byte
+// sectors per 4,096-graph batch, 16 wavefronts per unit to hide it) and, at
+// 40% of the issue slots, by the instructions around them.  The batch, ms per
+// launch: gathering every round 16.8; pushed masks with a chunk's scans and
+// pushes in lockstep 10.9; uncoloured vertices packed across chunks 8.2; a new
+// vertex for every lane that is done, winners pushing sixteen at a time 7.5.
+template <int BITS>
+__device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int L, int* left) {
+  __shared__ int sh_cnt;
+  const Slots<BITS> sl = Slots<BITS>::at(smem, g.n);
+  const auto state = [sl](int u) { return sl.state(u); };
+  int32_t* const skipv = g.out;  // the resume offsets, until the colours are written
+  const int lane = lane_id();
+  const int wave = threadIdx.x / kWave;
+  const int gl = lane & (L - 1), grp = lane / L, Gw = kWave / L;
+  const int nchunks = (g.n + kWave - 1) / kWave;
+  bool any = false;
+  int r = g.rounds_in;
+  if (BITS == 16)
+    for (int i = threadIdx.x; i < (g.n + 1) / 2; i += blockDim.x) sl.w[i] = 0;
+  for (int v = threadIdx.x; v < g.n; v += blockDim.x) {
+    const int s = r == 0 ? -1 : g.out[v];
+    if (BITS == 24) sl.w[v] = (uint32_t)s << 24;
+    else sl.set_state(v, s);
+    any |= s < 0;
+  }
+  __syncthreads();
+  if (r == 0) {
+    // round 1 in closed form (sorted rows): v keeps colour 0 iff no neighbour
+    // has a lower id
+    any = false;
+    Winners<BITS> wq;
+    for (int ch = wave; ch < nchunks; ch += kBatchWaves) {
+      const int v = ch * kWave + lane;
+      int b = 0, e = 0;
+      bool win = false;
+      if (v < g.n) {
+        b = g.rp[v];
+        e = g.rp[v + 1];
+        win = e == b || g.ci[b] > v;
+        if (win) sl.set_state(v, 0);
+        skipv[v] = 0;
+        any |= !win;
+      }
+      wq.add(sl, g.ci, __ballot(win && e > b), b, e, 0);
+      if (wq.cnt >= kPushBatch) wq.flush(sl, g.ci);
+    }
+    wq.flush(sl, g.ci);
+    r = g.n > 0 ? 1 : 0;
+  } else {
+    // resumed: the masks of the uncoloured vertices from their rows
+    for (int ch = wave; ch < nchunks; ch += kBatchWaves) {
+      const int v = ch * kWave + lane;
+      int b = 0, e = 0;
+      bool act = false;
+      if (v < g.n) {
+        skipv[v] = 0;
+        act = sl.state(v) < 0;
+      }
+      if (act) {
+        b = g.rp[v];
+        e = g.rp[v + 1];
+      }
+      const uint64_t am = __ballot(act);
+      const int cnt = __popcll(am);
+      for (int p = 0; p < cnt; p += Gw) {
+        const int k = p + grp;
+        const int pos = nth_set_bit(am, k < cnt ? k : 0);
+        const int vb = __shfl(b, pos), ve = __shfl(e, pos);
+        uint32_t m = 0;
+        if (k < cnt) {
+          const Quads q = quads_of(g.ci, vb, ve);
+          for (int i = gl; 4 * i < q.len; i += L) {
+            int u[4];
+            unpack(q.q[i], u);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (4 * i + j >= q.lead && 4 * i + j < q.len) {
+                const int c = sl.state(u[j]);
+                if (c >= 0 && c < BITS) m |= 1u << c;
+              }
+          }
+        }
+        for (int off = L / 2; off > 0; off >>= 1) m |= (uint32_t)__shfl_xor((int)m, off);
+        if (k < cnt && gl == 0 && m) sl.mark(ch * kWave + pos, m);
+      }
+    }
+  }
+  bool more = __syncthreads_or(any);
+  // (r < n: every round colours the lowest uncoloured vertex, so R <= n;
+  // the bound only stops a broken invariant from spinning forever, and the
+  // graph then reports uncoloured vertices)
+  while (more && r < g.n && (g.max_rounds <= 0 || r - g.rounds_in < g.max_rounds)) {
+    ++r;
+    for (int ch = wave; ch < nchunks; ch += kBatchWaves) {  // speculate
+      const int v = ch * kWave + lane;
+      bool full = false;
+      if (v < g.n && sl.state(v) < 0) {
+        const uint32_t m = sl.mask(v);
+        full = m == kAllTaken<BITS>;
+        if (!full) sl.set_state(v, ~__builtin_ctz(~m));
+      }
+      const uint64_t fm = __ballot(full);
+      if (fm == 0) continue;
+      int b = 0, e = 0;
+      if (full) {
+        b = g.rp[v];
+        e = g.rp[v + 1];
+      }
+      const int cnt = __popcll(fm);
+      for (int p = 0; p < cnt; p += Gw) {
+        const int k = p + grp;
+        const int pos = nth_set_bit(fm, k < cnt ? k : 0);
+        const int vb = __shfl(b, pos), ve = __shfl(e, pos);
+        if (k < cnt) {
+          const int t = spec_quads(g.ci, state, vb, ve, L, gl, BITS);
+          if (gl == 0) sl.set_state(ch * kWave + pos, ~t);
+        }
+      }
+    }
+    __syncthreads();
+    // Detect, commit, push.  A wavefront packs the uncoloured vertices of its
+    // chunks into batches of 64 whose row ends and offsets are loaded ahead.
+    // Each lane scans a row, eight entries (two quads) a step, and takes the
+    // next vertex of the batch as soon as its own is decided, so that every
+    // step has 64 rows to read and a long scan holds up no other; the winners
+    // push sixteen at a time while the next step's quads are on their way.
+    bool lost = false;
+    Winners<BITS> wq;
+    int ch = wave, pv = 0, pc = 0;  // next chunk; vertices packed so far, in lanes 0 .. pc - 1
+    auto next_batch = [&](int& v) {
+      while (ch < nchunks) {  // wave-uniform
+        const int c0 = ch * kWave;
+        ch += kBatchWaves;
+        const uint64_t am = __ballot(c0 + lane < g.n && sl.state(min(c0 + lane, g.n - 1)) < 0);
+        const int total = pc + __popcll(am);
+        if (total == pc) continue;
+        const int q = pack_lanes(am, c0 + lane, pc);  // beyond lane 63 it wraps to lane 0
+        if (lane >= pc) pv = q;
+        pc = total;
+        if (total < kWave) continue;
+        v = pv;
+        pv = q;
+        pc = total - kWave;
+        return kWave;
+      }
+      v = pv;
+      const int c = pc;
+      pc = 0;
+      return c;
+    };
+    int qv = 0, qb = 0, qe = 0, qs = 0, qc = 0, qh = 0;  // the batch being handed out, its head
+    int nv = 0, nb = 0, ne = 0, ns = 0;                  // the one after it
+    auto load_next = [&]() {
+      const int c = next_batch(nv);
+      if (lane < c) {
+        nb = g.rp[nv];
+        ne = g.rp[nv + 1];
+        ns = skipv[nv];
+      }
+      return c;
+    };
+    int nc = load_next();
+    // this lane's scan: vertex v (-1: none), colour t, row [b, e); lo is where it
+    // began, k the aligned entry of the step, first the first uncoloured lower
+    // neighbour seen (-1: none); all but v and t are positions in colidx
+    int v = -1, t = 0, b = 0, e = 0, lo = 0, k = 0, first = -1;
+    // the scan of a lane ends at position `at`
+    auto settle = [&](bool done, bool lose, int at) {
+      const int sk = first >= 0 ? first : at;
+      const bool win = done && !lose;
+      if (win) sl.set_state(v, t);
+      else if (done && sk != lo) skipv[v] = sk - b;
+      lost |= done && lose;
+      wq.add(sl, g.ci, __ballot(win && t < BITS && sk < e), sk, e, t);
+      if (done) v = -1;
+    };
+    const int mis = (int)(((uintptr_t)g.ci >> 2) & 3);
+    for (;;) {  // wave-uniform
+      for (;;) {
+        const uint64_t fm = __ballot(v < 0);
+        if (fm == 0 || (qh == qc && nc == 0)) break;
+        if (qh == qc) {
+          qv = nv;
+          qb = nb;
+          qe = ne;
+          qs = ns;
+          qc = nc;
+          qh = 0;
+          nc = load_next();
+        }
+        const int take = min(__popcll(fm), qc - qh);
+        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(fm >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)fm, 0));
+        const int from = (qh + rank) & (kWave - 1);
+        const int xv = __shfl(qv, from), xb = __shfl(qb, from), xe = __shfl(qe, from),
+                  xs = __shfl(qs, from);
+        if (v < 0 && rank < take) {
+          v = xv;
+          b = xb;
+          e = xe;
+          lo = xb + xs;
+          k = ((lo + mis) & ~3) - mis;
+          first = -1;
+          t = ~sl.state(v);
+        }
+        qh += take;
+      }
+      const uint64_t am = __ballot(v >= 0);
+      const int cnt = __popcll(am);
+      if (cnt == 0) break;
+      if (cnt <= kSparseChunk) {  // (no vertex is left to hand out)
+        // a group of lanes each for the rest
+        const int GL = group_lanes(cnt);
+        const int gi = lane / GL;
+        const int pos = __shfl(pack_lanes(am, lane), gi);
+        const int vv = __shfl(v, pos), vb = __shfl(b, pos), ve = __shfl(e, pos),
+                  vt = __shfl(t, pos);
+        int gsk = __shfl(max(k, lo) - b, pos), glose = 0;
+        if (gi < cnt) {  // group-uniform
+          const uint64_t gmask = GL == kWave ? ~0ull : ((1ull << GL) - 1) << (gi * GL);
+          glose = detect_quads(g.ci, state, vb, ve, vv, vt, GL, lane & (GL - 1), gmask, gi * GL,
+                               &gsk);
+        }
+        const int src = v >= 0 ? __popcll(am & ((1ull << lane) - 1)) * GL : 0;
+        const int osk = __shfl(gsk, src), olose = __shfl(glose, src);
+        settle(v >= 0, olose != 0, b + osk);
+        break;
+      }
+      int4 wa = make_int4(0, 0, 0, 0), wb = wa;
+      if (v >= 0) {
+        if (k < e) wa = *(const int4*)(g.ci + k);
+        if (k + 4 < e) wb = *(const int4*)(g.ci + k + 4);
+      }
+      if (wq.cnt >= kPushBatch) wq.flush(sl, g.ci);
+      int u[8], s[8];
+      unpack(wa, u);
+      unpack(wb, u + 4);
+      // An id of v or above ends the scan; such an entry (and one outside the
+      // row, masked below) reads v's own state instead.
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s[j] = v >= 0 ? sl.state((int)min((unsigned)u[j], (unsigned)v)) : 0;
+      uint32_t past = 0, hit = 0, open = 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        past |= (uint32_t)((unsigned)u[j] >= (unsigned)v) << j;
+        // decode, do not test the sign: a neighbour that wins in this same pass
+        // flips ~t to t concurrently and must still count
+        hit |= (uint32_t)(tent_of(s[j]) == t) << j;
+        open |= (uint32_t)(s[j] < 0) << j;
+      }
+      past |= ~0u << min(max(e - k, 0), 8);
+      const uint32_t seen = 0xffu & (~0u << min(max(lo - k, 0), 8));
+      const uint32_t stop = (past | hit) & seen;
+      const bool done = v >= 0 && stop != 0;
+      const int at = stop ? __builtin_ctz(stop) : 8;
+      const uint32_t before = open & seen & ((1u << at) - 1);
+      if (first < 0 && before) first = k + __builtin_ctz(before);
+      settle(done, !((past >> at) & 1), k + at);
+      k += 8;
+    }
+    wq.flush(sl, g.ci);
+    more = __syncthreads_or(lost);
+  }
+  if (threadIdx.x == 0) sh_cnt = 0;
+  __syncthreads();
+  int mine = 0;
+  for (int v = threadIdx.x; v < g.n; v += blockDim.x) {
+    const int s = sl.state(v);
+    g.out[v] = s;
+    mine += s < 0;
+  }
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
+  if (lane_id() == 0 && mine) atomicAdd(&sh_cnt, mine);
+  __syncthreads();
+  *left = sh_cnt;
+  __syncthreads();
+  return r;
+}
+
 // Barrier of the K workgroups of a team.  Every member runs: each holds
 // one of the team's K consecutive queue entries, a workgroup takes its next
 // entry only after finishing its graph, and the graphs of earlier entries
 // never wait on later ones, so the members of the earliest unfinished team
-// are all taken (the launch is at most two workgroups per compute unit, all
+// are all taken (the launch is one workgroup per compute unit, all
 // resident).  As the persistent kernel's grid barrier: agent-scope release
 // and acquire around one arrival counter; a wait beyond the spin limit sets
 // the team's abort flag, after which the team's barriers return at once.
@@ -629,6 +1072,8 @@ __device__ __forceinline__ int run_team(const GraphRun& g, char* smem, TeamCtrl*
 
 __device__ __forceinline__ int dispatch_state(const GraphRun& g, int maxdeg, char* smem, int L,
                                               int* left) {
+  if (maxdeg <= 127 && Slots<24>::fits(g.n)) return run_graph_push<24>(g, smem, L, left);
+  if (maxdeg <= 127 && Slots<16>::fits(g.n)) return run_graph_push<16>(g, smem, L, left);
   if (maxdeg <= 127 && g.n <= kBatchLds) return run_graph<int8_t, true>(g, (int8_t*)smem, L, left);
   if (maxdeg <= 32767 && 2 * g.n <= kBatchLds)
     return run_graph<int16_t, true>(g, (int16_t*)smem, L, left);
@@ -636,7 +1081,7 @@ __device__ __forceinline__ int dispatch_state(const GraphRun& g, int maxdeg, cha
   return run_graph<int32_t, false>(g, g.out, L, left);
 }
 
-__global__ __launch_bounds__(kBatchBlock, 8) void k_batch_color(gc_graph_desc* d,
+__global__ __launch_bounds__(kBatchBlock, 4) void k_batch_color(gc_graph_desc* d,
                                                             const int32_t* rowptr_base,
                                                             const int32_t* colidx_base,
                                                             int32_t* colors_base, int max_rounds,
@@ -710,20 +1155,17 @@ __global__ void k_batch_rounds_out(int64_t G, const gc_graph_desc* d, int32_t* r
   for (long g = tid; g < G; g += nth) rounds_out[g] = d[g].rounds;
 }
 
-// Two workgroups per compute unit (two 64 KB LDS slices per 160 KB), all
-// resident at once, whatever the number of graphs: a team can use workgroups
-// beyond one per graph.
-static int batch_grid() {
+static int batch_cus() {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 1;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 1;
-  return 2 * (cus > 0 ? cus : 1);
+  return cus > 0 ? cus : 1;
 }
 
 static int run_batch(int64_t G, gc_graph_desc* d, const int32_t* rpb, const int32_t* cib,
                      int32_t* colb, int max_rounds, void* ws, hipStream_t s) {
   static bool lds_set = false;
-  if (!lds_set) {  // allow the 64 KB dynamic slice on top of the static LDS
+  if (!lds_set) {  // allow the dynamic slice on top of the static LDS
     hipError_t e = hipFuncSetAttribute((const void*)k_batch_color,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kBatchLds);
     if (e != hipSuccess) return (int)e;
@@ -734,7 +1176,9 @@ static int run_batch(int64_t G, gc_graph_desc* d, const int32_t* rpb, const int3
   int32_t* order = (int32_t*)((char*)ws + ws_order_off());
   int32_t* slot = (int32_t*)((char*)ws + ws_slot_off(G));
   int32_t* gk = (int32_t*)((char*)ws + ws_gk_off(G));
-  const int grid = batch_grid();
+  // one workgroup per compute unit, all resident at once, whatever the number
+  // of graphs: a team can use workgroups beyond one per graph
+  const int grid = batch_cus();
   hipLaunchKernelGGL(k_batch_plan, dim3(1), dim3(1024), 0, s, G, d, rpb, order, slot, gk, teams,
                      ctrl, grid);
   hipError_t e = hipGetLastError();

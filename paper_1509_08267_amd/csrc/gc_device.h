@@ -55,6 +55,17 @@ __device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {
   return pos;
 }
 
+// Packing the lanes of m: the lane that holds rank r among them (bit order)
+// sends x to lane (from + r) % 64, the other lanes fill up behind, so the call
+// is one permutation of the wavefront (all lanes must be active).
+__device__ __forceinline__ int pack_lanes(uint64_t m, int x, int from = 0) {
+  const int lane = lane_id();
+  const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+  const int to = ((m >> lane) & 1) ? rank : __popcll(m) + lane - rank;
+  return __builtin_amdgcn_ds_permute(((from + to) & (kWave - 1)) * 4, x);
+}
+
 __device__ __forceinline__ void store_system(int32_t* p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
