@@ -222,8 +222,10 @@ enum gc_algorithm {
                         vertex refreshes its slots for neighbours in other
                         blocks and is recoloured if one in a higher block has
                         its colour.  The colouring depends on p by design;
-                        R <= p.  4 bytes per CSR entry of device memory; the
-                        rounds are driven from the host                       */
+                        R <= p.  The rounds are driven from the host.  Up to a
+                        maximum degree of 126 and 256 vertices per block the
+                        slots are kept as masks (25 to 49 bytes per vertex of
+                        device memory), else as 4 bytes per CSR entry         */
 };
 enum gc_mode {
   GC_MODE_AUTO = 0,       /* currently GRAPH                                      */

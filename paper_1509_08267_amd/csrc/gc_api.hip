@@ -123,6 +123,8 @@ struct gc_ctx {
   int64_t partitions = 0;    // p of GC_ALGO_BLOCKS (0 = auto)
   int32_t* bslot = nullptr;  // device, nnz: ForbiddenColors slots (GC_ALGO_BLOCKS)
   uint8_t* btodo = nullptr;  // device, n
+  uint64_t* bmask = nullptr; // device, (2 + bwords) * n: the masks in the place of the slots
+  int bwords = 0;
 
   // data-flow pass of GC_ALGO_SEQ, allocated on first use
   void* word = nullptr;         // device, n words
@@ -317,6 +319,7 @@ static void free_ctx(gc_ctx* h) {
   if (h->o_colors) (void)hipFree(h->o_colors);
   if (h->bslot) (void)hipFree(h->bslot);
   if (h->btodo) (void)hipFree(h->btodo);
+  if (h->bmask) (void)hipFree(h->bmask);
   if (h->word) (void)hipFree(h->word);
   if (h->starts) (void)hipFree(h->starts);
   if (h->unit_part) (void)hipFree(h->unit_part);
@@ -569,6 +572,94 @@ static int permute_back(gc_ctx* h, const int32_t* coloured, int32_t* colors_out,
   return GC_OK;
 }
 
+// Algorithm 1 with p blocks by masks instead of slots (gc_blocks.hip): rounds
+// queued eight at a time, or all of them once their number is known, and a
+// flag read back after them.
+static int color_blocks_masks(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStream_t s) {
+  const int64_t p = partitions_of(h);
+  const int64_t per_block = (h->n + p - 1) / p;  // vertices of a block at most
+  const int words = per_block <= 64 ? 1 : per_block <= 128 ? 2 : 4;
+  if (!h->btodo || words > h->bwords) {
+    int rc = ensure_idle(h);
+    if (rc) return rc;
+    if (h->bmask) (void)hipFree(h->bmask);
+    h->bmask = nullptr;
+    h->bwords = 0;
+    hipError_t e = hipMalloc((void**)&h->bmask, (size_t)(2 + words) * h->n * sizeof(uint64_t));
+    if (e == hipSuccess && !h->btodo) e = hipMalloc((void**)&h->btodo, (size_t)h->n);
+    if (e != hipSuccess) return set_err(h, GC_ENOMEM, "block masks: %s", hipGetErrorString(e));
+    h->bwords = words;
+  }
+  h->stats_ready = false;
+  KArgs a = make_args(h, colors_out, light_max_of(h, auto_lanes(h)));
+  a.push = 0;
+  gc::BArgs b{};
+  b.rowptr = h->rowptr;
+  b.colidx = h->colidx;
+  b.todo = h->btodo;
+  b.n = (int32_t)h->n;
+  b.p = p;
+  b.ctrl = h->ctrl;
+  b.st = (int8_t*)h->state;
+  b.mask = h->bmask;
+  b.nb = h->bmask + 2 * h->n;
+  b.words = words;
+  // whole blocks, at most 64 vertices of them (block_start rounds up: one more
+  // than the average can fall into a range)
+  b.unit = std::max<int64_t>(1, 63 * p / h->n);
+  b.part = h->part;
+  const int grid = round_grid(h);
+  const int64_t units = (p + b.unit - 1) / b.unit;
+  const int grid1 = (int)std::max<int64_t>(
+      1, std::min<int64_t>(grid_of(h), (units + gc::kWavesPerBlock - 1) / gc::kWavesPerBlock));
+  LCHECK(h, gc::launch_init(a, s));
+  if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[0], s));
+  LCHECK(h, gc::launch_blkm_init(b, h->rp64, grid, s));
+  if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[1], s));
+  int r = 0;  // last round queued
+  int64_t K = h->known_rounds > 0 ? h->known_rounds : 8;
+  for (;;) {
+    int64_t upto = r + K;
+    if (h->max_rounds > 0) upto = std::min<int64_t>(upto, h->max_rounds);
+    while (r < upto) {
+      b.round = ++r;
+      b.count_left = r == h->max_rounds;
+      if (h->profile) {  // phase 1 and phase 2 between events, as speculate and detect
+        int rc = reserve_round_events(h, r > h->rev_rounds ? std::max(r, 2 * h->rev_rounds) : r);
+        if (rc) return rc;
+        HIPCHECK(h, hipEventRecord(h->rev[3 * (r - 1)], s));
+      }
+      LCHECK(h, gc::launch_blkm_phase(b, h->rp64, 1, grid1, s));
+      if (h->profile) HIPCHECK(h, hipEventRecord(h->rev[3 * (r - 1) + 1], s));
+      LCHECK(h, gc::launch_blkm_phase(b, h->rp64, 2, grid, s));
+      if (h->profile) {
+        HIPCHECK(h, hipEventRecord(h->rev[3 * (r - 1) + 2], s));
+        h->timed_rounds = r;
+      }
+    }
+    HIPCHECK(h, hipMemcpyAsync(&h->host->flag, &h->ctrl->more[(r + 1) % 3].v, sizeof(int32_t),
+                               hipMemcpyDeviceToHost, s));
+    HIPCHECK(h, hipStreamSynchronize(s));
+    if (!h->host->flag) break;
+    if (h->max_rounds > 0 && r >= h->max_rounds) break;
+    // Lemma 2: at most p rounds (p + 1 as the paper states it)
+    if (r > p + 1) return set_err(h, GC_EDEVICE, "round %d > p + 1 = %lld: the p-block "
+                                  "colouring is not converging (internal error)", r,
+                                  (long long)(p + 1));
+    K = 8;
+  }
+  if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));
+  LCHECK(h, gc::launch_finish(a, 1, h->fin_dev, s));
+  if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[3], s));
+  h->pending_profile = h->profile;
+  int rc = permute_back(h, colors_out, user_out, s);
+  if (rc) return rc;
+  HIPCHECK(h, hipEventRecord(h->done, s));
+  h->in_flight = true;
+  h->stats_ready = true;
+  return GC_OK;
+}
+
 // Algorithm 1 with p blocks (GC_ALGO_BLOCKS): per-edge slots, p sequential
 // blocks per round; the host reads the count of vertices to recolour after
 // each round (R <= p).
@@ -576,7 +667,7 @@ static int color_blocks(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipSt
   int rc = GC_OK;
   if (h->n > 0 && !h->bslot) {
     hipError_t e = hipMalloc((void**)&h->bslot, (size_t)std::max<int64_t>(h->m, 1) * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&h->btodo, (size_t)h->n);
+    if (e == hipSuccess && !h->btodo) e = hipMalloc((void**)&h->btodo, (size_t)h->n);
     if (e != hipSuccess) return set_err(h, GC_ENOMEM, "block slots: %s", hipGetErrorString(e));
   }
   h->stats_ready = false;
@@ -754,7 +845,12 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
     if (rc) return rc;
   }
   (void)hipGetLastError();  // launch checks below must see only this call's errors
-  if (h->algorithm == GC_ALGO_BLOCKS) return color_blocks(h, colors_out, user_out, s);
+  if (h->algorithm == GC_ALGO_BLOCKS) {
+    const bool masks = h->n > 0 && h->sbytes == 1 &&
+                       (h->n + partitions_of(h) - 1) / partitions_of(h) <= gc::kBlkMaxVertices;
+    return masks ? color_blocks_masks(h, colors_out, user_out, s)
+                 : color_blocks(h, colors_out, user_out, s);
+  }
   if (use_seq(h) && h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH)
     return color_flow(h, colors_out, user_out, s);
   if (use_push(h)) {

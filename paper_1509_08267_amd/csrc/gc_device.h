@@ -73,6 +73,28 @@ __device__ __forceinline__ void store_system(int32_t* p, int32_t v) {
 // tentative colour carried by a state word (final colours decode to themselves)
 __device__ __forceinline__ int tent_of(int s) { return s < 0 ? ~s : s; }
 
+// Sum of the per-workgroup counts of the last detect pass into the round
+// trace.  Run by every thread of one workgroup, after the kernel boundary (or
+// grid barrier) that follows that pass.
+__device__ inline void fold_trace(Ctrl* ctrl, const int32_t* part) {
+  __shared__ int sh[kWavesPerBlock];
+  const int r = ctrl->pend.v;
+  if (r == 0) return;
+  const int g = ctrl->pend_grid.v;
+  int sum = 0;
+  for (int i = threadIdx.x; i < g; i += blockDim.x) sum += part[i];
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane_id() == 0) sh[threadIdx.x / kWave] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kWavesPerBlock; ++w) sum += sh[w];
+    if (r - 1 < kTraceRounds) ctrl->trace[r - 1] = sum;
+    ctrl->pend.v = 0;
+  }
+  __syncthreads();
+}
+
 // ------------------------------------------- per-vertex work, L lanes --
 
 // Least colour not final on any neighbour of the row [b, e), computed by a

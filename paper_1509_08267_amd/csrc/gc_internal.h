@@ -168,13 +168,30 @@ struct BArgs {
   int64_t p;              // blocks
   int32_t round;          // round being run (1-based), for the trace
   Ctrl* ctrl;
+  // the passes that keep masks in the place of the slots (maximum degree at
+  // most 126, at most kBlkMaxVertices vertices per block)
+  int8_t* st;             // n: current colours, -1 before a vertex's first
+  uint64_t* mask;         // 2n: colours of the neighbours in other blocks after the last round
+                          // (bit c of the 128), of the vertices still to be (re)coloured
+  uint64_t* nb;           // words * n: neighbours in the vertex's own block, bit j the j-th
+                          // vertex of its unit
+  int32_t words;          // 64-vertex words of a unit
+  int64_t unit;           // blocks of a unit
+  int32_t* part;          // active vertices of each workgroup of the last phase 2
+  int32_t count_left;     // phase 2 adds the vertices to recolour into ctrl->left
 };
+constexpr int kBlkMaxVertices = 256;
 
 int launch_blocks_init(const BArgs& a, bool rp64, int grid, void* stream);
 // Phase 1 (phase = 1) or phase 2 (phase = 2) of one round; after phase 2,
 // ctrl->left holds the vertices to recolour and ctrl->trace / last_round the
 // round's size.
 int launch_blocks_phase(const BArgs& a, bool rp64, int phase, int grid, void* stream);
+// The same passes with masks: the in-block neighbours (once per call, before
+// round 1), then phase 1 or phase 2 of round a.round.  A phase of a round with no
+// vertex to recolour (ctrl->more) does nothing.
+int launch_blkm_init(const BArgs& a, bool rp64, int grid, void* stream);
+int launch_blkm_phase(const BArgs& a, bool rp64, int phase, int grid, void* stream);
 // ctrl->left = value (vertices still to recolour when a round cap stops the loop)
 int launch_blocks_set_left(Ctrl* c, int value, void* stream);
 

@@ -813,28 +813,6 @@ __device__ void publish_detect(const KArgs& a, int r, const Tally& tl, HeavySmem
   }
 }
 
-// Sum of the per-workgroup counts of the last detect pass into the round
-// trace.  Run by every thread of one workgroup, after the kernel boundary (or
-// grid barrier) that follows that pass.
-__device__ void fold_trace(const KArgs& a) {
-  __shared__ int sh[kWavesPerBlock];
-  const int r = a.ctrl->pend.v;
-  if (r == 0) return;
-  const int g = a.ctrl->pend_grid.v;
-  int sum = 0;
-  for (int i = threadIdx.x; i < g; i += blockDim.x) sum += a.part[i];
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-  if (lane_id() == 0) sh[threadIdx.x / kWave] = sum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < kWavesPerBlock; ++w) sum += sh[w];
-    if (r - 1 < kTraceRounds) a.ctrl->trace[r - 1] = sum;
-    a.ctrl->pend.v = 0;
-  }
-  __syncthreads();
-}
-
 // A whole phase of round r over every uncoloured vertex, by one block of a
 // grid of nblk blocks.  Detect also clears more[(r+2) % 3] for the round
 // after next.
@@ -866,7 +844,7 @@ __global__ __launch_bounds__(kBlock) void k_phase(KArgs a, int round, int from_b
   __shared__ HeavySmem sm;
   const int r = from_base ? a.ctrl->round_base.v + round : round;
   if (PHASE == kSpec && blockIdx.x == 0) {
-    fold_trace(a);
+    fold_trace(a.ctrl, a.part);
     // the previous round's push pass has run
     if (threadIdx.x == 0) *(uint64_t*)&a.ctrl->tasks = 0;
   }
@@ -1054,7 +1032,7 @@ __global__ void k_advance_base(Ctrl* c, int by) {
 template <typename S, bool VEC>
 __global__ __launch_bounds__(kBlock) void k_finish(KArgs a, int32_t* out) {
   __shared__ int sh_max[kWavesPerBlock], sh_left[kWavesPerBlock];
-  if (blockIdx.x == 0) fold_trace(a);  // the last detect pass's round size
+  if (blockIdx.x == 0) fold_trace(a.ctrl, a.part);  // the last detect pass's round size
   constexpr int V = 16 / (int)sizeof(S);
   const S* __restrict__ st = (const S*)a.st;
   int mx = -1, left = 0;
@@ -1176,7 +1154,7 @@ __global__ __launch_bounds__(kBlock) void k_persistent(KArgs a, int max_rounds) 
     const int more = __hip_atomic_load(&a.ctrl->more[r % 3].v, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
     if (!more) break;  // grid-uniform: read after a barrier, written before it
-    if (blockIdx.x == 0) fold_trace(a);
+    if (blockIdx.x == 0) fold_trace(a.ctrl, a.part);
     phase<RP, S, L, kSpec>(a, r, blockIdx.x, gridDim.x, sm);
     if (!grid_barrier(a.ctrl, epoch)) return;
     phase<RP, S, L, kDetect>(a, r, blockIdx.x, gridDim.x, sm);
