@@ -36,7 +36,7 @@ thread_local std::string tl_error;
 
 struct Pinned {  // read-back area in pinned host memory
   int32_t flag;
-  int32_t pad0;
+  int32_t size;
   int32_t counts[3];  // medium count, heavy count, max degree
   int32_t err[2];
   int32_t last_round;  // folded from fin by the host once a call has completed
@@ -133,6 +133,12 @@ struct gc_ctx {
   int64_t starts_room = 0;
   int32_t* unit_part = nullptr; // device, kUnitGrid + 1: per-workgroup unit counts, the number of units
   bool units_ready = false;
+
+  // core pass (gc_core.hip), decided from the graph alone
+  void* core = nullptr;      // device, kCoreBytes, allocated on first use
+  bool core_off = false;     // it gave up on this graph
+  int64_t core_round = -1;   // with R known: the core follows this round (-1: no core)
+  int64_t core_size = 0;     // and has so many vertices
 
   Captured chunk;  // discovery chunk (chunk_rounds)
   Captured exact;  // R - 1 rounds, once R is known
@@ -320,6 +326,7 @@ static void free_ctx(gc_ctx* h) {
   if (h->bslot) (void)hipFree(h->bslot);
   if (h->btodo) (void)hipFree(h->btodo);
   if (h->bmask) (void)hipFree(h->bmask);
+  if (h->core) (void)hipFree(h->core);
   if (h->word) (void)hipFree(h->word);
   if (h->starts) (void)hipFree(h->starts);
   if (h->unit_part) (void)hipFree(h->unit_part);
@@ -545,6 +552,7 @@ static int ensure_order(gc_ctx* h, hipStream_t s) {
   h->built_order = GC_ORDER_NATURAL;
   h->lists_dirty = true;
   h->known_rounds = 0;
+  h->core_off = false;
   if (h->order == GC_ORDER_NATURAL) return GC_OK;
   if (h->m > INT32_MAX)
     return set_err(h, GC_ETOOBIG, "vertex order: more than 2^31 - 1 CSR entries");
@@ -751,6 +759,7 @@ static int color_flow(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStre
   f.cbits = bits_of(h->maxdeg);
   f.wide = f.cbits + bits_of(h->n) > 32;
   if (f.wide) f.cbits = 32;
+  f.last = (int)h->known_rounds;  // (a graph that was changed is reported)
   f.ctrl = h->ctrl;
   const int wb = f.wide ? 8 : 4;
   const int64_t room = (h->n + gc::kWave - 1) / gc::kWave + 2 * ((int64_t)h->mcount + h->hcount) + 1;
@@ -817,6 +826,69 @@ static int color_flow(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStre
   return GC_OK;
 }
 
+// Whether calls in the current settings may end in the core pass.
+static bool may_use_core(const gc_ctx* h) {
+  return h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH && h->max_rounds == 0 && !use_seq(h) &&
+         h->algorithm != GC_ALGO_BLOCKS && !h->profile && !h->core_off;
+}
+
+// Rounds that the core pass has to replace to pay for collecting its vertices
+// and building their rows, about 45 us (uniform random graph of 10,000 vertices:
+// the last six rounds by it 197 us a call, by their own passes 182); a round of
+// the passes takes 12 us at least, one of the core 6 to 8.
+constexpr int64_t kCoreMinRounds = 10;
+
+// With R known, the round after which the core pass takes over: the first one
+// that leaves few enough vertices, if enough rounds follow.
+static int decide_core(gc_ctx* h) {
+  h->core_round = -1;
+  const int64_t R = h->known_rounds;
+  if (h->n <= gc::kCoreMax || R <= kCoreMinRounds || R > gc::kTraceRounds || !may_use_core(h))
+    return GC_OK;
+  int32_t* sizes = new (std::nothrow) int32_t[R];
+  if (!sizes) return GC_OK;
+  const hipError_t e = hipMemcpy(sizes, h->ctrl->trace, R * sizeof(int32_t), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) {
+    const int64_t r = std::lower_bound(sizes, sizes + R, (int32_t)gc::kCoreMax,
+                                       [](int32_t x, int32_t most) { return x > most; }) - sizes;
+    if (R - r >= kCoreMinRounds) {  // |U_{r + 1}| = sizes[r]
+      h->core_round = r;
+      h->core_size = sizes[r];
+    }
+  }
+  delete[] sizes;
+  HIPCHECK(h, e);
+  return GC_OK;
+}
+
+// The rounds after round0 as one core pass over at most `size` vertices.  A
+// call that does not know R yet waits for it: *gave_up says that it needs the
+// rounds' own passes after all.
+static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, bool* gave_up,
+                      hipStream_t s) {
+  if (!h->core) {
+    const hipError_t e = hipMalloc(&h->core, gc::kCoreBytes);
+    if (e != hipSuccess) return set_err(h, GC_ENOMEM, "core pass: %s", hipGetErrorString(e));
+  }
+  gc::CoreArgs c;
+  c.tents = (uint64_t*)h->core;
+  c.wins = c.tents + gc::kCoreMax / 2;
+  c.ids = (int32_t*)(c.wins + 2 * (gc::kCoreMax / 64));
+  c.part = c.ids + gc::kCoreMax;
+  LCHECK(h, gc::launch_core_collect(a, h->sbytes, c, s));
+  const int workgroups = (int)((size + gc::kWave - 1) / gc::kWave);
+  // (no round beyond the known ones: a graph that was changed is reported)
+  LCHECK(h, gc::launch_core(a, h->rp64, h->sbytes, c, round0, (int)h->known_rounds, workgroups, s));
+  *gave_up = false;
+  if (h->known_rounds == 0) {
+    HIPCHECK(h, hipMemcpyAsync(&h->host->flag, &h->ctrl->core_fail.v, sizeof(int32_t),
+                               hipMemcpyDeviceToHost, s));
+    HIPCHECK(h, hipStreamSynchronize(s));
+    *gave_up = h->host->flag != 0;
+  }
+  return GC_OK;
+}
+
 extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   if (!h) return set_err(nullptr, GC_EINVAL, "gc_color: NULL handle");
   if (h->n > 0 && !colors_out) return set_err(h, GC_EINVAL, "gc_color: colors_out is NULL");
@@ -853,7 +925,8 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   }
   if (use_seq(h) && h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH)
     return color_flow(h, colors_out, user_out, s);
-  if (use_push(h)) {
+  const bool all_core = may_use_core(h) && h->n <= gc::kCoreMax;
+  if (use_push(h) && !all_core) {
     if (!h->seen && h->n > 0) {
       const size_t nv = (size_t)(h->n + gc::kWave - 1) / gc::kWave * gc::kWave;  // whole chunks
       hipError_t e = hipMalloc((void**)&h->seen, nv * gc::kPushColors);
@@ -895,12 +968,18 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   h->stats_ready = false;
   const int L = auto_lanes(h);
   const int light = light_max_of(h, L);
-  const KArgs a = make_args(h, colors_out, light);
+  KArgs a = make_args(h, colors_out, light);
   const int grid = round_grid(h);
   const int mode = resolve_mode(h);
+  bool gave_up = false;
 
+  if (all_core) a.push = 0;  // (no flags to clear)
   LCHECK(h, gc::launch_init(a, s));
-  if (mode == GC_MODE_PERSISTENT) {
+  if (all_core) {
+    LCHECK(h, gc::launch_fill_tent0(a, h->sbytes, grid, s));
+    rc = color_core(h, a, 0, h->n, &gave_up, s);
+    if (rc) return rc;
+  } else if (mode == GC_MODE_PERSISTENT) {
     int maxg = 0;
     LCHECK(h, gc::persistent_max_grid(h->rp64, h->sbytes, L, &maxg));
     // persistent_max_grid bounds the grid by what the kernel's register and
@@ -931,8 +1010,10 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
       }
       h->timed_rounds = K;
     } else if (mode == GC_MODE_GRAPH && h->known_rounds > 0) {
-      // R is known: queue rounds 2..R in one captured chunk, no read-back.
-      const int K = (int)h->known_rounds - 1;
+      // R is known: queue rounds 2..R, or those before the core pass, in one
+      // captured chunk, no read-back.
+      const bool core = h->core_round >= 1 && may_use_core(h);
+      const int K = (int)(core ? h->core_round : h->known_rounds) - 1;
       if (K > 0) {
         if (!usable(h->exact, K, L, grid, a)) {
           rc = capture(h, h->exact, a, L, K);
@@ -940,14 +1021,28 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
         }
         HIPCHECK(h, hipGraphLaunch(h->exact.exec, s));
       }
+      if (core) {
+        rc = color_core(h, a, (int)h->core_round, h->core_size, &gave_up, s);
+        if (rc) return rc;
+      }
     } else {
       const int K = std::max(1, h->chunk_rounds);
       for (;;) {
+        // (|U_{r-1}|: the last size already in the trace)
+        const bool core = may_use_core(h) && r >= 2 && r - 2 < gc::kTraceRounds;
         HIPCHECK(h, hipMemcpyAsync(&h->host->flag, &h->ctrl->more[(r + 1) % 3].v, sizeof(int32_t),
                                    hipMemcpyDeviceToHost, s));
+        if (core)
+          HIPCHECK(h, hipMemcpyAsync(&h->host->size, &h->ctrl->trace[r - 2], sizeof(int32_t),
+                                     hipMemcpyDeviceToHost, s));
         HIPCHECK(h, hipStreamSynchronize(s));
         if (!h->host->flag) break;
         if (h->max_rounds > 0 && r >= h->max_rounds) break;
+        if (core && h->host->size <= gc::kCoreMax) {
+          rc = color_core(h, a, r, h->host->size, &gave_up, s);
+          if (rc) return rc;
+          break;
+        }
         // every round colours at least the lowest uncoloured vertex (Lemma 2
         // with one vertex per block), so R <= n: more rounds mean a broken
         // invariant, reported instead of looping
@@ -977,6 +1072,10 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
         }
       }
     }
+  }
+  if (gave_up) {  // once per graph: again, by the rounds' own passes
+    h->core_off = true;
+    return gc_color(h, user_out, stream);
   }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));
   LCHECK(h, gc::launch_finish(a, h->sbytes, h->fin_dev, s));
@@ -1023,7 +1122,10 @@ static int wait_done(gc_ctx* h) {
     return set_err(h, GC_EINVAL, "%d vertices uncoloured after the known %d rounds: the graph "
                    "changed after gc_create", h->host->left, h->host->last_round);
   }
-  if (h->max_rounds == 0) h->known_rounds = h->host->last_round;
+  if (h->max_rounds == 0 && h->known_rounds != h->host->last_round) {
+    h->known_rounds = h->host->last_round;
+    return decide_core(h);
+  }
   return GC_OK;
 }
 

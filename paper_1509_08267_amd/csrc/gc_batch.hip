@@ -134,7 +134,7 @@ __global__ void k_batch_descs(int64_t G, const int64_t* voff, const int64_t* eof
 //   sum(cost <= T) + kTeamCost * sum(work of the others),
 // and the T taken is the smallest one (of the histogram's bucket ends) that
 // nwg workgroups can hold.  A graph of cost above T and work of at least
-// kMinTeam is coloured by K = min(kTeamCost * work / T + 1, nwg,
+// kMinTeam is coloured by K = min(kTeamCost * work / T + 1, nwg / 2,
 // work / kMinTeamWork) workgroups when K >= 2 and a team slot and K - 1 extra
 // queue entries are left; its K entries are consecutive, with the team slot
 // beside them (-1 for a graph of one workgroup).  Also resets the work queue.
@@ -218,7 +218,9 @@ __global__ __launch_bounds__(1024) void k_batch_plan(int64_t G, const gc_graph_d
     uint64_t q = 0;
     if (w >= kMinTeam && cost_alone(d[g].n, w) > T) {
       q = kTeamCost * w / T + 1;
-      if (q > (uint64_t)nwg) q = (uint64_t)nwg;
+      // half the units at most: a team waits for all its members, and another
+      // kernel that needs its workgroups resident together may hold the rest
+      if (q > (uint64_t)(nwg + 1) / 2) q = (uint64_t)(nwg + 1) / 2;
       if (q > w / kMinTeamWork) q = w / kMinTeamWork;
     }
     int k = 1, s = -1;

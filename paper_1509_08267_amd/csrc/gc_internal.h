@@ -64,6 +64,8 @@ struct Ctrl {
   Line pend;             // round whose per-workgroup counts in KArgs::part are not yet in
                          // trace (0: none)
   Line pend_grid;        // workgroups of that round's detect pass
+  Line core_n;           // vertices of the core pass (gc_core.hip)
+  Line core_fail;        // it gave up: a colour beyond its masks
   Line ticket;           // next unit of the data-flow pass (GC_ALGO_SEQ)
   Line over;             // its vertices of a round beyond the trace
   Line tasks;            // 64-bit: push tasks (high half) and their pieces (low half)
@@ -129,6 +131,27 @@ struct KArgs {
   Ctrl* ctrl;
 };
 
+// Scratch of the core pass (gc_core.hip).
+constexpr int kCoreMax = 4096;  // core vertices at most
+constexpr int kCoreGrid = 256;  // workgroups of the collecting pass at most
+struct CoreArgs {
+  int32_t* ids;      // kCoreMax: the core vertices in id order
+  int32_t* part;     // kCoreGrid: uncoloured vertices per workgroup of the collecting pass
+  uint64_t* tents;   // kCoreMax / 2: published tentative colours, round << 32 | two of them
+  uint64_t* wins;    // 2 * kCoreMax / 64: published winners, round << 32 | 32 of them
+};
+constexpr size_t kCoreBytes = (size_t)kCoreMax * 4 + kCoreGrid * 4 + (size_t)kCoreMax / 2 * 8 +
+                              (size_t)2 * (kCoreMax / 64) * 8;
+// The uncoloured vertices of a.st become the core (ctrl->core_n of them).
+int launch_core_collect(const KArgs& a, int sbytes, const CoreArgs& c, void* stream);
+// The remaining rounds, the first of them round0 + 1 and none after round
+// `last` (0: no bound), by 64 core vertices per workgroup; ctrl->core_fail says
+// when it gave up (vertices stay uncoloured).
+int launch_core(const KArgs& a, bool rp64, int sbytes, const CoreArgs& c, int round0, int last,
+                int workgroups, void* stream);
+// Every vertex uncoloured with tentative colour 0 (what precedes round 1).
+int launch_fill_tent0(const KArgs& a, int sbytes, int grid, void* stream);
+
 // Arguments of the data-flow pass of the id-priority schedule (gc_seq.hip).
 struct FlowArgs {
   const void* rowptr;     // int32 or int64, n + 1
@@ -139,6 +162,7 @@ struct FlowArgs {
   int32_t light_max;      // deg <= light_max: a lane per vertex, above: a wavefront
   int32_t sorted;         // rows ascending: a row is read up to its first id above the vertex
   int32_t wide;           // 64-bit words (cbits = 32): colours and rounds don't fit 32 bits together
+  int32_t last;           // > 0: vertices of a later round are reported uncoloured
   int32_t cbits;          // bits of a colour (at most the maximum degree) in a word
   const int32_t* starts;  // first id of each unit, and n behind the last
   const int32_t* units;   // their number

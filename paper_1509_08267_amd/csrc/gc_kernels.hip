@@ -1011,6 +1011,8 @@ __global__ void k_init(KArgs a) {
     a.ctrl->bar.v = 0;
     a.ctrl->abort.v = 0;
     a.ctrl->left.v = 0;
+    a.ctrl->core_n.v = 0;
+    a.ctrl->core_fail.v = 0;
     a.ctrl->ticket.v = 0;
     a.ctrl->over.v = 0;
     *(uint64_t*)&a.ctrl->tasks = 0;
@@ -1329,6 +1331,15 @@ int persistent_max_grid(bool rp64, int sbytes, int lanes, int* grid_out) {
 int launch_init(const KArgs& a, void* stream) {
   hipLaunchKernelGGL(k_init, dim3(a.push && a.clear_seen ? 1024 : 64), dim3(kBlock), 0,
                      (hipStream_t)stream, a);
+  return (int)hipGetLastError();
+}
+
+int launch_fill_tent0(const KArgs& a, int sbytes, int grid, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  if (sbytes == 1) hipLaunchKernelGGL((k_fill_tent0<int8_t>), dim3(grid), dim3(kBlock), 0, s, a);
+  else if (sbytes == 2)
+    hipLaunchKernelGGL((k_fill_tent0<int16_t>), dim3(grid), dim3(kBlock), 0, s, a);
+  else hipLaunchKernelGGL((k_fill_tent0<int32_t>), dim3(grid), dim3(kBlock), 0, s, a);
   return (int)hipGetLastError();
 }
 

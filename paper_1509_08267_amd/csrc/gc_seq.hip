@@ -272,7 +272,8 @@ __global__ __launch_bounds__(kBlock) void k_flow_finish(FlowArgs a, int32_t* out
   const long tid = blockIdx.x * (long)blockDim.x + threadIdx.x;
   const long nth = (long)gridDim.x * blockDim.x;
   for (long v = tid; v < a.n; v += nth) {
-    const W w = word[v];
+    W w = word[v];
+    if (a.last > 0 && (w >> a.cbits) > (W)a.last) w = 0;
     const int c = w ? (int)(w & cmask) : -1;
     const int r = (int)(w >> a.cbits);
     a.colors[v] = c;
