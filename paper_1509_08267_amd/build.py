@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgc.so")
 SOURCES = ["gc_api.hip", "gc_kernels.hip", "gc_batch.hip", "gc_blocks.hip", "gc_core.hip",
-           "gc_order.hip", "gc_seq.hip", "gc_validate.hip"]
+           "gc_order.hip", "gc_resident.hip", "gc_seq.hip", "gc_validate.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

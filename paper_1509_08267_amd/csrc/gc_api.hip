@@ -137,6 +137,8 @@ struct gc_ctx {
   // core pass (gc_core.hip), decided from the graph alone
   void* core = nullptr;      // device, kCoreBytes, allocated on first use
   bool core_off = false;     // it gave up on this graph
+  uint64_t* res = nullptr;   // resident pass (gc_resident.hip): device, resident_bytes(n)
+  bool res_off = false;      // it gave up on this graph
   int64_t core_round = -1;   // with R known: the core follows this round (-1: no core)
   int64_t core_size = 0;     // and has so many vertices
 
@@ -327,6 +329,7 @@ static void free_ctx(gc_ctx* h) {
   if (h->btodo) (void)hipFree(h->btodo);
   if (h->bmask) (void)hipFree(h->bmask);
   if (h->core) (void)hipFree(h->core);
+  if (h->res) (void)hipFree(h->res);
   if (h->word) (void)hipFree(h->word);
   if (h->starts) (void)hipFree(h->starts);
   if (h->unit_part) (void)hipFree(h->unit_part);
@@ -552,7 +555,7 @@ static int ensure_order(gc_ctx* h, hipStream_t s) {
   h->built_order = GC_ORDER_NATURAL;
   h->lists_dirty = true;
   h->known_rounds = 0;
-  h->core_off = false;
+  h->core_off = h->res_off = false;
   if (h->order == GC_ORDER_NATURAL) return GC_OK;
   if (h->m > INT32_MAX)
     return set_err(h, GC_ETOOBIG, "vertex order: more than 2^31 - 1 CSR entries");
@@ -826,10 +829,15 @@ static int color_flow(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStre
   return GC_OK;
 }
 
-// Whether calls in the current settings may end in the core pass.
-static bool may_use_core(const gc_ctx* h) {
+// Whether calls in the current settings may run rounds in one launch: in the
+// core pass, or all of them in the resident pass.
+static bool may_fuse_rounds(const gc_ctx* h) {
   return h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH && h->max_rounds == 0 && !use_seq(h) &&
-         h->algorithm != GC_ALGO_BLOCKS && !h->profile && !h->core_off;
+         h->algorithm != GC_ALGO_BLOCKS && !h->profile;
+}
+static bool may_use_core(const gc_ctx* h) { return may_fuse_rounds(h) && !h->core_off; }
+static bool use_resident(const gc_ctx* h) {
+  return may_fuse_rounds(h) && !h->res_off && gc::resident_fits(h->n, h->m, h->sbytes);
 }
 
 // Rounds that the core pass has to replace to pay for collecting its vertices
@@ -861,6 +869,14 @@ static int decide_core(gc_ctx* h) {
   return GC_OK;
 }
 
+static int read_gave_up(gc_ctx* h, bool* gave_up, hipStream_t s) {
+  HIPCHECK(h, hipMemcpyAsync(&h->host->flag, &h->ctrl->core_fail.v, sizeof(int32_t),
+                             hipMemcpyDeviceToHost, s));
+  HIPCHECK(h, hipStreamSynchronize(s));
+  *gave_up = h->host->flag != 0;
+  return GC_OK;
+}
+
 // The rounds after round0 as one core pass over at most `size` vertices.  A
 // call that does not know R yet waits for it: *gave_up says that it needs the
 // rounds' own passes after all.
@@ -870,6 +886,7 @@ static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, bool*
     const hipError_t e = hipMalloc(&h->core, gc::kCoreBytes);
     if (e != hipSuccess) return set_err(h, GC_ENOMEM, "core pass: %s", hipGetErrorString(e));
   }
+  *gave_up = false;
   gc::CoreArgs c;
   c.tents = (uint64_t*)h->core;
   c.wins = c.tents + gc::kCoreMax / 2;
@@ -879,14 +896,18 @@ static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, bool*
   const int workgroups = (int)((size + gc::kWave - 1) / gc::kWave);
   // (no round beyond the known ones: a graph that was changed is reported)
   LCHECK(h, gc::launch_core(a, h->rp64, h->sbytes, c, round0, (int)h->known_rounds, workgroups, s));
-  *gave_up = false;
-  if (h->known_rounds == 0) {
-    HIPCHECK(h, hipMemcpyAsync(&h->host->flag, &h->ctrl->core_fail.v, sizeof(int32_t),
-                               hipMemcpyDeviceToHost, s));
-    HIPCHECK(h, hipStreamSynchronize(s));
-    *gave_up = h->host->flag != 0;
+  return h->known_rounds == 0 ? read_gave_up(h, gave_up, s) : GC_OK;
+}
+
+// The whole colouring in one resident pass.
+static int color_resident(gc_ctx* h, const KArgs& a, bool* gave_up, hipStream_t s) {
+  if (!h->res) {
+    const hipError_t e = hipMalloc((void**)&h->res, gc::resident_bytes(h->n));
+    if (e != hipSuccess) return set_err(h, GC_ENOMEM, "resident pass: %s", hipGetErrorString(e));
   }
-  return GC_OK;
+  *gave_up = false;
+  LCHECK(h, gc::launch_resident(a, h->rp64, gc::ResArgs{h->res}, (int)h->known_rounds, s));
+  return h->known_rounds == 0 ? read_gave_up(h, gave_up, s) : GC_OK;
 }
 
 extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
@@ -925,8 +946,9 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   }
   if (use_seq(h) && h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH)
     return color_flow(h, colors_out, user_out, s);
-  const bool all_core = may_use_core(h) && h->n <= gc::kCoreMax;
-  if (use_push(h) && !all_core) {
+  const bool resident = use_resident(h);
+  const bool all_core = !resident && may_use_core(h) && h->n <= gc::kCoreMax;
+  if (use_push(h) && !all_core && !resident) {
     if (!h->seen && h->n > 0) {
       const size_t nv = (size_t)(h->n + gc::kWave - 1) / gc::kWave * gc::kWave;  // whole chunks
       hipError_t e = hipMalloc((void**)&h->seen, nv * gc::kPushColors);
@@ -973,9 +995,12 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   const int mode = resolve_mode(h);
   bool gave_up = false;
 
-  if (all_core) a.push = 0;  // (no flags to clear)
+  if (all_core || resident) a.push = 0;  // (no flags to clear)
   LCHECK(h, gc::launch_init(a, s));
-  if (all_core) {
+  if (resident) {
+    rc = color_resident(h, a, &gave_up, s);
+    if (rc) return rc;
+  } else if (all_core) {
     LCHECK(h, gc::launch_fill_tent0(a, h->sbytes, grid, s));
     rc = color_core(h, a, 0, h->n, &gave_up, s);
     if (rc) return rc;
@@ -1074,7 +1099,7 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
     }
   }
   if (gave_up) {  // once per graph: again, by the rounds' own passes
-    h->core_off = true;
+    (resident ? h->res_off : h->core_off) = true;
     return gc_color(h, user_out, stream);
   }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));

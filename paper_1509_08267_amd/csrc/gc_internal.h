@@ -149,6 +149,21 @@ int launch_core_collect(const KArgs& a, int sbytes, const CoreArgs& c, void* str
 // when it gave up (vertices stay uncoloured).
 int launch_core(const KArgs& a, bool rp64, int sbytes, const CoreArgs& c, int round0, int last,
                 int workgroups, void* stream);
+// The resident pass (gc_resident.hip).
+constexpr int kResGroups = 64;         // workgroups at most
+constexpr int kResMaxChunks = 6;       // 64-vertex chunks of one at most: 24,576 vertices
+constexpr int kResLds = 78 * 1024;     // LDS of one (two to a compute unit)
+struct ResArgs {
+  uint64_t* words;  // resident_bytes(n): the published words
+};
+size_t resident_bytes(int64_t n);
+// Whether a graph's rows (on average) and states fit; one-byte states only.
+bool resident_fits(int64_t n, int64_t m, int sbytes);
+// The whole colouring, states into a.st (all of them written unless `last` > 0
+// stops it), rounds and round sizes into ctrl; ctrl->core_fail is set and
+// nothing else done when a workgroup's rows don't fit.
+int launch_resident(const KArgs& a, bool rp64, const ResArgs& r, int last, void* stream);
+
 // Every vertex uncoloured with tentative colour 0 (what precedes round 1).
 int launch_fill_tent0(const KArgs& a, int sbytes, int grid, void* stream);
 

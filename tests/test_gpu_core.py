@@ -1,5 +1,6 @@
-"""GPU: the core pass (the last rounds, or all rounds of a small graph, in one
-launch) at the edges of its ranges: workgroup remainders (63, 64, 65 vertices),
+"""GPU: the core pass (the last rounds, or all rounds of a small graph with
+degrees above 126, in one launch) at the edges of its ranges: workgroup
+remainders (191, 192, 193 vertices),
 the largest core (4,096 vertices) and one vertex more, the last colour with a
 mask bit (511) and the first without, rows long enough for a whole workgroup,
 all three state widths, both row layouts and offset widths, pushed and
@@ -24,17 +25,15 @@ def _clique_over_leaves(k, leaves):
 
 
 CASES = {
-    "one": lambda: graphgen.empty(1),
-    "edgeless": lambda: graphgen.empty(130),
-    "n63": lambda: graphgen.er(63, 400, 1),
-    "n64": lambda: graphgen.er(64, 400, 2),
-    "n65": lambda: graphgen.er(65, 400, 3),
-    "n4096": lambda: graphgen.er(4096, 60_000, 4),
-    "n4097": lambda: graphgen.er(4097, 60_000, 5),
+    "n191": lambda: graphgen.er(191, 16_500, 1),
+    "n192": lambda: graphgen.er(192, 16_500, 2),
+    "n193": lambda: graphgen.er(193, 16_500, 3),
+    "star": lambda: graphgen.star(200, 100),
+    "n4096": lambda: graphgen.er(4096, 350_000, 4),
+    "n4097": lambda: graphgen.er(4097, 350_000, 5),
     "dense": lambda: graphgen.er(5000, 1_500_000, 6),
     "K512": lambda: graphgen.complete(512),
     "K513": lambda: graphgen.complete(513),
-    "path": lambda: graphgen.path(700),
     "star_wide_state": lambda: graphgen.star(40_000, 20_000),
     "long_rows": lambda: _clique_over_leaves(20, 8_500),
     "rmat": lambda: graphgen.rmat(15, 16, seed=3),
@@ -70,7 +69,7 @@ def test_core_on_four_streams_at_once():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_1509_08267_amd import gc
-    g = graphgen.er(4096, 60_000, 7)
+    g = graphgen.er(4096, 350_000, 7)
     ref = oracle.rsc(g.rowptr, g.colidx)
     rp, ci = torch.from_numpy(g.rowptr).cuda(), torch.from_numpy(g.colidx).cuda()
     torch.cuda.synchronize()
