@@ -1168,29 +1168,56 @@ __global__ __launch_bounds__(kBlock) void k_persistent(KArgs a, int max_rounds) 
 
 // Degree classes: medium (light_max < deg < heavy_min) and heavy
 // (deg >= heavy_min) vertex lists; counts[2] receives the maximum degree.
+// One atomic per wavefront and list or workgroup, and at most kClassifyBlocks
+// workgroups: they all meet on the same three words (2,000 vertices 27.7 -> 3.6
+// us; R-MAT of scale 22, 279 K medium vertices, 340 -> 322).
+constexpr int kClassifyBlocks = 512;
+
 template <typename RP>
-__global__ void k_classify(const RP* rowptr, int32_t n, int32_t light_max, int32_t heavy_min,
-                           int32_t* mlist, int32_t* hlist, int32_t* counts, int32_t* widx) {
-  __shared__ int sh_max;
-  if (threadIdx.x == 0) sh_max = 0;
-  __syncthreads();
+__global__ __launch_bounds__(kBlock) void k_classify(const RP* rowptr, int32_t n, int32_t light_max,
+                                                     int32_t heavy_min, int32_t* mlist,
+                                                     int32_t* hlist, int32_t* counts,
+                                                     int32_t* widx) {
+  __shared__ int sh_max[kWavesPerBlock];
+  const int lane = lane_id();
+  // the slots of the lanes in m, behind the list's earlier entries
+  auto slot = [&](uint64_t m, int32_t* count) {
+    int base = 0;
+    if (lane == 0 && m) base = atomicAdd(count, __popcll(m));
+    return __shfl(base, 0) + __popcll(m & ((1ull << lane) - 1));
+  };
   int mx = 0;
-  const long tid = blockIdx.x * (long)blockDim.x + threadIdx.x;
   const long nth = (long)gridDim.x * blockDim.x;
-  for (long v = tid; v < n; v += nth) {
-    RP d = rowptr[v + 1] - rowptr[v];
-    int di = d > (RP)INT_MAX ? INT_MAX : (int)d;
+  for (long v0 = blockIdx.x * (long)blockDim.x + threadIdx.x - lane; v0 < n; v0 += nth) {
+    const long v = v0 + lane;  // (wave-uniform loop)
+    RP d = 0;
+    if (v < n) d = rowptr[v + 1] - rowptr[v];
+    const int di = d > (RP)INT_MAX ? INT_MAX : (int)d;
     mx = di > mx ? di : mx;
+    const bool big = v < n && di > light_max, heavy = big && di >= heavy_min;
+    const uint64_t mm = __ballot(big && !heavy), hm = __ballot(heavy);
     int w = -1;  // wide block: medium i -> i; heavy j -> mcount + j (set afterwards)
-    if (di > light_max) {
-      if (di >= heavy_min) hlist[atomicAdd(&counts[1], 1)] = (int)v;
-      else mlist[w = atomicAdd(&counts[0], 1)] = (int)v;
+    if (mm) {
+      const int i = slot(mm, &counts[0]);
+      if (big && !heavy) mlist[w = i] = (int)v;
     }
-    widx[v] = w;
+    if (hm) {
+      const int i = slot(hm, &counts[1]);
+      if (heavy) hlist[i] = (int)v;
+    }
+    if (v < n) widx[v] = w;
   }
-  atomicMax(&sh_max, mx);
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    const int o = __shfl_xor(mx, off);
+    mx = o > mx ? o : mx;
+  }
+  if (lane == 0) sh_max[threadIdx.x / kWave] = mx;
   __syncthreads();
-  if (threadIdx.x == 0) atomicMax(&counts[2], sh_max);
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kWavesPerBlock; ++w) mx = sh_max[w] > mx ? sh_max[w] : mx;
+    atomicMax(&counts[2], mx);
+  }
 }
 
 // ------------------------------------------------------ host launchers --
@@ -1368,6 +1395,7 @@ int launch_finish(const KArgs& a, int sbytes, int32_t* out, void* stream) {
 int launch_classify(const void* rowptr, bool rp64, int32_t n, int32_t light_max, int32_t heavy_min,
                     int32_t* mlist, int32_t* hlist, int32_t* counts, int32_t* widx, int grid,
                     void* stream) {
+  grid = std::max(1, std::min(std::min(grid, kClassifyBlocks), (n + kBlock - 1) / kBlock));
   if (rp64)
     hipLaunchKernelGGL(k_classify<int64_t>, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream,
                        (const int64_t*)rowptr, n, light_max, heavy_min, mlist, hlist, counts, widx);

@@ -30,6 +30,11 @@ namespace {
 //   7 edge (v, u) without (u, v)
 // Without SORTED a row's entries are compared pairwise (the fallback when
 // an ascending copy cannot be made).
+// kRowLanes lanes share a row: an entry's check is a chain of dependent loads
+// (the search of the neighbour's row), and a lane that walked a row alone ran
+// its entries' chains one after the other (2,000 vertices of average degree 20:
+// 58 us, now 6.5).
+constexpr int kRowLanes = 16;
 template <typename RP, bool SORTED>
 __global__ void k_validate(const RP* rowptr, const int32_t* colidx, int32_t n, int64_t m,
                            int32_t* err) {
@@ -40,13 +45,14 @@ __global__ void k_validate(const RP* rowptr, const int32_t* colidx, int32_t n, i
     if (code <= old) err[1] = (int)where;
   };
   if (tid == 0 && (rowptr[0] != 0 || (int64_t)rowptr[n] != m)) fail(1, 0);
-  for (long v = tid; v < n; v += nth) {
+  const int gl = tid % kRowLanes;
+  for (long v = tid / kRowLanes; v < n; v += nth / kRowLanes) {
     RP b = rowptr[v], e = rowptr[v + 1];
     if (e < b || b < 0 || (int64_t)e > m) {
       fail(2, v);
       continue;
     }
-    for (RP k = b; k < e; ++k) {
+    for (RP k = b + gl; k < e; k += kRowLanes) {
       int u = colidx[k];
       if (u < 0 || u >= n) {
         fail(3, v);
