@@ -2,16 +2,17 @@
 // management, argument checks, the round drivers and result read-back.
 //
 // Round drivers (GC_OPT_MODE):
-//   GRAPH       (default) rounds run as captured hipGraphs of K rounds each
-//               (speculate + detect launches with a device-side round base),
-//               so back-to-back kernels need no host launch per round.  The
-//               first call on a handle learns the round count R with one
-//               4-byte read-back per chunk; because R is a function of the
-//               (unchanged) graph alone, later calls queue exactly R - 1
-//               rounds after round 1 and never wait on the host.  If the
-//               graph was modified against the contract, vertices are left
-//               uncoloured and gc_get_stats reports it.
-//   CHUNKED     as GRAPH with direct launches.
+//   GRAPH       (default) the first call on a handle queues rounds in chunks and
+//               learns the round count R from one look at the stream per
+//               chunk; because R is a function of the (unchanged) graph alone,
+//               later calls queue exactly the rounds it takes, as a captured
+//               hipGraph (speculate + detect launches with a device-side round
+//               base), and never wait on the host.  Small graphs, the last
+//               rounds of larger ones and sequential First Fit run several
+//               rounds in one launch instead (gc_resident.hip, gc_core.hip,
+//               gc_seq.hip).  If the graph was modified against the contract,
+//               vertices are left uncoloured and gc_get_stats reports it.
+//   CHUNKED     rounds queued in chunks on every call, a look per chunk.
 //   HOST        one speculate + detect pair per round, then a read-back.
 //   PERSISTENT  one cooperative launch runs every round with grid barriers.
 // All drivers run the same phase code and give the same bits.
@@ -36,7 +37,7 @@ thread_local std::string tl_error;
 
 struct Pinned {  // read-back area in pinned host memory
   int32_t flag;
-  int32_t size;
+  int32_t pad0;
   int32_t counts[3];  // medium count, heavy count, max degree
   int32_t err[2];
   int32_t last_round;  // folded from fin by the host once a call has completed
@@ -142,7 +143,6 @@ struct gc_ctx {
   int64_t core_round = -1;   // with R known: the core follows this round (-1: no core)
   int64_t core_size = 0;     // and has so many vertices
 
-  Captured chunk;  // discovery chunk (chunk_rounds)
   Captured exact;  // R - 1 rounds, once R is known
 
   // profiling (GC_OPT_PROFILE): events around the kernels of a call
@@ -301,7 +301,6 @@ static void drop(Captured& c) {
 
 static void free_ctx(gc_ctx* h) {
   if (!h) return;
-  drop(h->chunk);
   drop(h->exact);
   for (hipEvent_t& e : h->pev)
     if (e) (void)hipEventDestroy(e);
@@ -869,24 +868,12 @@ static int decide_core(gc_ctx* h) {
   return GC_OK;
 }
 
-static int read_gave_up(gc_ctx* h, bool* gave_up, hipStream_t s) {
-  HIPCHECK(h, hipMemcpyAsync(&h->host->flag, &h->ctrl->core_fail.v, sizeof(int32_t),
-                             hipMemcpyDeviceToHost, s));
-  HIPCHECK(h, hipStreamSynchronize(s));
-  *gave_up = h->host->flag != 0;
-  return GC_OK;
-}
-
-// The rounds after round0 as one core pass over at most `size` vertices.  A
-// call that does not know R yet waits for it: *gave_up says that it needs the
-// rounds' own passes after all.
-static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, bool* gave_up,
-                      hipStream_t s) {
+// The rounds after round0 as one core pass over at most `size` vertices.
+static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, hipStream_t s) {
   if (!h->core) {
     const hipError_t e = hipMalloc(&h->core, gc::kCoreBytes);
     if (e != hipSuccess) return set_err(h, GC_ENOMEM, "core pass: %s", hipGetErrorString(e));
   }
-  *gave_up = false;
   gc::CoreArgs c;
   c.tents = (uint64_t*)h->core;
   c.wins = c.tents + gc::kCoreMax / 2;
@@ -896,18 +883,17 @@ static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, bool*
   const int workgroups = (int)((size + gc::kWave - 1) / gc::kWave);
   // (no round beyond the known ones: a graph that was changed is reported)
   LCHECK(h, gc::launch_core(a, h->rp64, h->sbytes, c, round0, (int)h->known_rounds, workgroups, s));
-  return h->known_rounds == 0 ? read_gave_up(h, gave_up, s) : GC_OK;
+  return GC_OK;
 }
 
 // The whole colouring in one resident pass.
-static int color_resident(gc_ctx* h, const KArgs& a, bool* gave_up, hipStream_t s) {
+static int color_resident(gc_ctx* h, const KArgs& a, hipStream_t s) {
   if (!h->res) {
     const hipError_t e = hipMalloc((void**)&h->res, gc::resident_bytes(h->n));
     if (e != hipSuccess) return set_err(h, GC_ENOMEM, "resident pass: %s", hipGetErrorString(e));
   }
-  *gave_up = false;
   LCHECK(h, gc::launch_resident(a, h->rp64, gc::ResArgs{h->res}, (int)h->known_rounds, s));
-  return h->known_rounds == 0 ? read_gave_up(h, gave_up, s) : GC_OK;
+  return GC_OK;
 }
 
 extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
@@ -993,16 +979,16 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   KArgs a = make_args(h, colors_out, light);
   const int grid = round_grid(h);
   const int mode = resolve_mode(h);
-  bool gave_up = false;
+  bool fused = resident || all_core;  // the core or the resident pass has been queued
 
-  if (all_core || resident) a.push = 0;  // (no flags to clear)
+  if (fused) a.push = 0;  // (no flags to clear)
   LCHECK(h, gc::launch_init(a, s));
   if (resident) {
-    rc = color_resident(h, a, &gave_up, s);
+    rc = color_resident(h, a, s);
     if (rc) return rc;
   } else if (all_core) {
     LCHECK(h, gc::launch_fill_tent0(a, h->sbytes, grid, s));
-    rc = color_core(h, a, 0, h->n, &gave_up, s);
+    rc = color_core(h, a, 0, h->n, s);
     if (rc) return rc;
   } else if (mode == GC_MODE_PERSISTENT) {
     int maxg = 0;
@@ -1047,63 +1033,51 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
         HIPCHECK(h, hipGraphLaunch(h->exact.exec, s));
       }
       if (core) {
-        rc = color_core(h, a, (int)h->core_round, h->core_size, &gave_up, s);
+        rc = color_core(h, a, (int)h->core_round, h->core_size, s);
         if (rc) return rc;
+        fused = true;
       }
     } else {
       const int K = std::max(1, h->chunk_rounds);
-      for (;;) {
-        // (|U_{r-1}|: the last size already in the trace)
-        const bool core = may_use_core(h) && r >= 2 && r - 2 < gc::kTraceRounds;
-        HIPCHECK(h, hipMemcpyAsync(&h->host->flag, &h->ctrl->more[(r + 1) % 3].v, sizeof(int32_t),
-                                   hipMemcpyDeviceToHost, s));
-        if (core)
-          HIPCHECK(h, hipMemcpyAsync(&h->host->size, &h->ctrl->trace[r - 2], sizeof(int32_t),
-                                     hipMemcpyDeviceToHost, s));
-        HIPCHECK(h, hipStreamSynchronize(s));
-        if (!h->host->flag) break;
-        if (h->max_rounds > 0 && r >= h->max_rounds) break;
-        if (core && h->host->size <= gc::kCoreMax) {
-          rc = color_core(h, a, r, h->host->size, &gave_up, s);
-          if (rc) return rc;
-          break;
+      // rounds of a chunk; the first one is queued without a look at round 1
+      bool look = mode == GC_MODE_HOST || h->max_rounds > 0 || h->n == 0;
+      for (;; look = true) {
+        if (look) {
+          LCHECK(h, gc::launch_report(a, r, h->fin_dev, s));
+          HIPCHECK(h, hipStreamSynchronize(s));
+          if (!h->host->fin[0]) break;
+          if (h->max_rounds > 0 && r >= h->max_rounds) break;
+          if (may_use_core(h) && h->host->fin[1] <= gc::kCoreMax) {
+            rc = color_core(h, a, r, h->host->fin[1], s);
+            if (rc) return rc;
+            fused = true;
+            break;
+          }
         }
         // every round colours at least the lowest uncoloured vertex (Lemma 2
         // with one vertex per block), so R <= n: more rounds mean a broken
         // invariant, reported instead of looping
         if (r > h->n) return set_err(h, GC_EDEVICE, "round %d > n = %lld: the colouring is not "
                                      "converging (internal error)", r, (long long)h->n);
-        if (mode == GC_MODE_HOST) {
-          ++r;
-          LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 0, r, false, grid, s));
-          LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 1, r, false, grid, s));
-        } else if (mode == GC_MODE_CHUNKED) {
-          int upto = r + K;
-          if (h->max_rounds > 0) upto = std::min(upto, h->max_rounds);
-          for (int q = r + 1; q <= upto; ++q) {
-            LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 0, q, false, grid, s));
-            LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 1, q, false, grid, s));
-          }
-          r = upto;
-        } else if (mode == GC_MODE_GRAPH) {
-          if (!usable(h->chunk, K, L, grid, a)) {
-            rc = capture(h, h->chunk, a, L, K);
-            if (rc) return rc;
-          }
-          HIPCHECK(h, hipGraphLaunch(h->chunk.exec, s));
-          r += K;  // rounds r+1 .. r+K ran (the round base advanced by K)
-        } else {
-          return set_err(h, GC_EINVAL, "unknown mode %d", mode);
+        int upto = mode == GC_MODE_HOST ? r + 1 : r + K;
+        if (h->max_rounds > 0) upto = std::min(upto, h->max_rounds);
+        for (int q = r + 1; q <= upto; ++q) {
+          LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 0, q, false, grid, s));
+          LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 1, q, false, grid, s));
         }
+        r = upto;
       }
     }
   }
-  if (gave_up) {  // once per graph: again, by the rounds' own passes
-    (resident ? h->res_off : h->core_off) = true;
-    return gc_color(h, user_out, stream);
-  }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));
   LCHECK(h, gc::launch_finish(a, h->sbytes, h->fin_dev, s));
+  if (fused && h->known_rounds == 0) {
+    HIPCHECK(h, hipStreamSynchronize(s));
+    if (h->host->fin[4]) {  // once per graph: again, by the rounds' own passes
+      (resident ? h->res_off : h->core_off) = true;
+      return gc_color(h, user_out, stream);
+    }
+  }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[3], s));
   h->pending_profile = h->profile && mode != GC_MODE_PERSISTENT;
   rc = permute_back(h, colors_out, user_out, s);

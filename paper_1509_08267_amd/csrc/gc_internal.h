@@ -35,7 +35,7 @@ constexpr int kDeferRow = 512;      // a wavefront- or workgroup-class winner wi
                                     // than this left to push queues them for the grid-wide push pass
 constexpr int kPieceEntries = 1024; // row entries of one piece of that pass: one workgroup,
                                     // four entries per thread in flight, one step
-constexpr int kFinishHeader = 4;   // its leading output words (see launch_finish)
+constexpr int kFinishHeader = 5;   // its leading output words (see launch_finish)
 constexpr int kFinishWords = kFinishHeader + 2 * kFinishBlocks;
 
 // One 128-byte line per field that different blocks write, so that flags and
@@ -254,12 +254,16 @@ int launch_round1(const KArgs& a, bool rp64, int sbytes, int lanes, int grid, vo
 int launch_round(const KArgs& a, bool rp64, int sbytes, int lanes, int phase /*0 spec, 1 detect*/,
                  int round, bool round_from_base, int grid, void* stream);
 int launch_advance_base(const KArgs& a, int by, void* stream);
+// Into pinned memory, after round `round`: out[0] whether vertices are left,
+// out[1] the round's size |U_round|.
+int launch_report(const KArgs& a, int round, int32_t* out, void* stream);
 // The state becomes the caller's int32 colours.  `out` (kFinishWords words of
 // device-visible pinned host memory) receives, by system-scope stores:
 //   out[0] last round, out[1] abort flag, out[2] uncoloured count recorded by
-//   earlier passes (ctrl->left), out[3] workgroups G of this pass, and for
-//   each workgroup b < G: out[4 + 2b] = its largest colour + 1 (0 if none),
-//   out[5 + 2b] = its uncoloured vertices.
+//   earlier passes (ctrl->left), out[3] workgroups G of this pass, out[4]
+//   whether the core or resident pass gave up, and for each workgroup b < G:
+//   out[5 + 2b] = its largest colour + 1 (0 if none), out[6 + 2b] = its
+//   uncoloured vertices.
 // The host folds them once the stream has passed this kernel.
 int launch_finish(const KArgs& a, int sbytes, int32_t* out, void* stream);
 int launch_persistent(const KArgs& a, bool rp64, int sbytes, int lanes, int max_rounds, int grid,

@@ -1024,6 +1024,14 @@ __global__ void k_advance_base(Ctrl* c, int by) {
   if (threadIdx.x == 0 && blockIdx.x == 0) c->round_base.v += by;
 }
 
+__global__ __launch_bounds__(kBlock) void k_report(KArgs a, int round, int32_t* out) {
+  fold_trace(a.ctrl, a.part);
+  if (threadIdx.x == 0) {
+    store_system(&out[0], a.ctrl->more[(round + 1) % 3].v);
+    store_system(&out[1], round <= kTraceRounds ? a.ctrl->trace[round - 1] : INT32_MAX);
+  }
+}
+
 // Widening pass and statistics: the state becomes the caller's int32
 // colours, and each workgroup reports the largest colour and the uncoloured
 // count of its vertices straight into pinned host memory (layout at
@@ -1089,6 +1097,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(KArgs a, int32_t* out) {
       store_system(&out[1], a.ctrl->abort.v);
       store_system(&out[2], a.ctrl->left.v);
       store_system(&out[3], (int32_t)gridDim.x);
+      store_system(&out[4], a.ctrl->core_fail.v);
     }
   }
 }
@@ -1372,6 +1381,11 @@ int launch_fill_tent0(const KArgs& a, int sbytes, int grid, void* stream) {
 
 int launch_advance_base(const KArgs& a, int by, void* stream) {
   hipLaunchKernelGGL(k_advance_base, dim3(1), dim3(64), 0, (hipStream_t)stream, a.ctrl, by);
+  return (int)hipGetLastError();
+}
+
+int launch_report(const KArgs& a, int round, int32_t* out, void* stream) {
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(kBlock), 0, (hipStream_t)stream, a, round, out);
   return (int)hipGetLastError();
 }
 

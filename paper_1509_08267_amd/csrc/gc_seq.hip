@@ -341,6 +341,7 @@ __global__ __launch_bounds__(kBlock) void k_flow_finish(FlowArgs a, int32_t* out
     store_system(&out[1], agent(&a.ctrl->abort.v));
     store_system(&out[2], 0);
     store_system(&out[3], (int32_t)gridDim.x);
+    store_system(&out[4], 0);
   }
 }
 
