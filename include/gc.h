@@ -152,7 +152,8 @@ enum gc_option {
   GC_OPT_LANES = 2,          /* lanes per light vertex, 1,2,4,..,64; 0 = auto (from
                                 the average degree)                                */
   GC_OPT_HEAVY_DEGREE = 3,   /* deg >= this: a whole workgroup per vertex (4096)     */
-  GC_OPT_BLOCKS_PER_CU = 4,  /* workgroups per compute unit of the round kernels (8) */
+  GC_OPT_BLOCKS_PER_CU = 4,  /* workgroups per compute unit of the round kernels (6;
+                                5 with int64 row pointers)                         */
   GC_OPT_MAX_ROUNDS = 5,     /* stop after this many rounds (0 = no cap); leftover
                                 vertices make gc_get_stats return GC_EROUNDS       */
   GC_OPT_CHUNK_ROUNDS = 6,   /* rounds queued per read-back in CHUNKED/GRAPH (8)     */

@@ -109,7 +109,7 @@ struct gc_ctx {
   int lanes = 0;          // 0 = auto
   int medium_min = 0;     // 0 = auto (deg > medium threshold -> medium)
   int heavy_min = 4096;   // deg >= heavy_min -> heavy
-  int blocks_per_cu = 8;
+  int blocks_per_cu = 0;  // 0 = auto (blocks_per_cu_of)
   int persist_per_cu = 4; // co-resident workgroups per CU of the persistent kernel
   int max_rounds = 0;
   int chunk_rounds = 16;
@@ -259,7 +259,19 @@ static KArgs make_args(const gc_ctx* h, int32_t* colors, int light_max) {
   return a;
 }
 
-static int grid_of(const gc_ctx* h) { return std::max(1, h->cus * h->blocks_per_cu); }
+// Workgroups per CU of the round kernels.  No more than their registers let a
+// CU hold at once (7 with 32-bit row pointers, 5 with 64-bit ones): the rest
+// would start when the first are done, a second, nearly empty wave of them.
+// With 32-bit pointers one less is faster still, as more wavefronts only
+// compete for the caches.  Whole calls in ms at 5 / 6 / 7 / 8: uniform random
+// 2^24 edges 0.98 / 1.00 / 1.04 / 1.05, 160^3 stencil 3.15 / 3.13 / 3.58 /
+// 3.53, with 64-bit pointers 2^24 edges 0.97 / 1.01 / 1.04 / 1.04, R-MAT of
+// scale 22 14.97 / 16.6 / 16.4 / 15.8.
+static int blocks_per_cu_of(const gc_ctx* h) {
+  return h->blocks_per_cu > 0 ? h->blocks_per_cu : h->rp64 ? 5 : 6;
+}
+
+static int grid_of(const gc_ctx* h) { return std::max(1, h->cus * blocks_per_cu_of(h)); }
 
 // Workgroups of the round kernels: at most blocks_per_cu per CU, and no more
 // than the graph can keep busy (a wavefront per 64-vertex chunk or per medium
@@ -1238,7 +1250,7 @@ extern "C" int gc_get_option(gc_handle h, int option, int64_t* value) {
     case GC_OPT_LANES: *value = auto_lanes(h); return GC_OK;
     case GC_OPT_MEDIUM_DEGREE: *value = light_max_of(h, auto_lanes(h)); return GC_OK;
     case GC_OPT_HEAVY_DEGREE: *value = h->heavy_min; return GC_OK;
-    case GC_OPT_BLOCKS_PER_CU: *value = h->blocks_per_cu; return GC_OK;
+    case GC_OPT_BLOCKS_PER_CU: *value = blocks_per_cu_of(h); return GC_OK;
     case GC_OPT_MAX_ROUNDS: *value = h->max_rounds; return GC_OK;
     case GC_OPT_CHUNK_ROUNDS: *value = h->chunk_rounds; return GC_OK;
     case GC_OPT_MAX_DEGREE: *value = h->maxdeg; return GC_OK;
