@@ -446,6 +446,51 @@ __device__ __forceinline__ bool detect_lane_skip(const int32_t* __restrict__ col
   return false;
 }
 
+// The conflict scan of a whole unsorted row by one lane for its own vertex: does
+// a lower-id neighbour of v that is still uncoloured carry tentative colour t?
+// Eight entries in flight, up to the first conflict.  A chunk's vertices are
+// scanned side by side; by groups of lanes, eight vertices at a time, the pass
+// was one chain of loads after the other (300,007 vertices, 2.7 M edges, whole
+// call: 338 us by groups, 273 by lanes; four entries in flight 281).
+template <typename RP, typename S>
+__device__ __forceinline__ bool detect_lane(const int32_t* __restrict__ colidx,
+                                            const S* __restrict__ st, RP b, RP e, int v, int t) {
+  for (RP k = b; k < e; k += 8) {
+    int u[8], s[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) u[j] = k + j < e ? colidx[k + j] : INT32_MAX;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s[j] = u[j] < v ? (int)st[u[j]] : -1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      // decode, do not test the sign, as in the sorted scans
+      if (u[j] < v && tent_of(s[j]) == t) return true;
+  }
+  return false;
+}
+
+// The same by a group of GL lanes, four entries per lane in flight.
+template <typename RP, typename S>
+__device__ __forceinline__ bool detect_group4(const int32_t* __restrict__ colidx,
+                                              const S* __restrict__ st, RP b, RP e, int v, int t,
+                                              int GL, int gl, uint64_t gmask) {
+  for (RP kb = b; kb < e; kb += 4 * GL) {  // group-uniform
+    int u[4], s[4];
+    bool hit = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const RP k = kb + j * GL + gl;
+      u[j] = k < e ? colidx[k] : INT32_MAX;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] = u[j] < v ? (int)st[u[j]] : -1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hit |= u[j] < v && tent_of(s[j]) == t;
+    if (__ballot(hit) & gmask) return true;
+  }
+  return false;
+}
+
 // The pushes of several winners of one wave, spread over all 64 lanes: lane i
 // contributes the row segment [pb, pb + len) of its own winner (len = 0 for
 // none) with colour t.  The segments are concatenated in lane order; entry j

@@ -364,11 +364,12 @@ __device__ void light_phase(const KArgs& a, long wave_gid, long nwaves, Tally& t
     }
     const uint64_t am = __ballot(act);
     if (am == 0) continue;
-    if (PHASE == kDetect && sorted) {
-      // sorted rows: each lane scans for its own vertex (most scans stop
-      // within a few entries), then the chunk's winners push together.  A
-      // chunk with at most kSparseChunk uncoloured vertices (the later rounds)
-      // gives each of them a group of 64 / 2^ceil(log2 count) lanes instead.
+    if (PHASE == kDetect) {
+      // Each lane scans for its own vertex (most scans stop within a few
+      // entries), then the chunk's winners push together.  A chunk with at
+      // most kSparseChunk uncoloured vertices (the later rounds) gives each of
+      // them a group of 64 / 2^ceil(log2 count) lanes instead.  Unsorted rows
+      // are scanned from their start.
       const int t = ~s;
       RP pb = 0;
       int len = 0;
@@ -384,12 +385,16 @@ __device__ void light_phase(const KArgs& a, long wave_gid, long nwaves, Tally& t
         const int vv = (int)(ch * kWave) + pos;
         int sk = 0, lose = 0;
         if (valid) {  // group-uniform
-          const int sk0 = a.skip[vv];
-          sk = sk0;
           const uint64_t gmask = GL == kWave ? ~0ull : ((1ull << GL) - 1) << (g * GL);
-          lose = detect_group4_skip<RP, S>(a.colidx, st, vb, ve, vv, vt, GL, lane % GL, gmask,
-                                           g * GL, &sk);
-          if (lane % GL == 0 && sk != sk0) a.skip[vv] = sk;
+          if (sorted) {
+            const int sk0 = a.skip[vv];
+            sk = sk0;
+            lose = detect_group4_skip<RP, S>(a.colidx, st, vb, ve, vv, vt, GL, lane % GL, gmask,
+                                             g * GL, &sk);
+            if (lane % GL == 0 && sk != sk0) a.skip[vv] = sk;
+          } else {
+            lose = detect_group4<RP, S>(a.colidx, st, vb, ve, vv, vt, GL, lane % GL, gmask);
+          }
         }
         // back to the owning lanes: the vertex of lane v is the rank-th active one
         const int src = act ? __popcll(am & ((1ull << lane) - 1)) * GL : 0;
@@ -406,10 +411,16 @@ __device__ void light_phase(const KArgs& a, long wave_gid, long nwaves, Tally& t
           tl.active += 1;
         }
       } else if (act) {
-        const int sk0 = a.skip[v];
-        int sk = sk0;
-        const bool lose = detect_lane_skip<RP, S>(a.colidx, st, b, e, v, t, &sk);
-        if (sk != sk0) a.skip[v] = sk;
+        int sk = 0;
+        bool lose;
+        if (sorted) {
+          const int sk0 = a.skip[v];
+          sk = sk0;
+          lose = detect_lane_skip<RP, S>(a.colidx, st, b, e, v, t, &sk);
+          if (sk != sk0) a.skip[v] = sk;
+        } else {
+          lose = detect_lane<RP, S>(a.colidx, st, b, e, v, t);
+        }
         if (!lose) {
           st[v] = (S)t;
           pb = b + sk;
@@ -432,10 +443,9 @@ __device__ void light_phase(const KArgs& a, long wave_gid, long nwaves, Tally& t
       const int pos = nth_set_bit(am, valid ? k : 0);
       const RP vb = shfl_any<RP>(b, pos);
       const RP ve = shfl_any<RP>(e, pos);
-      const int vs = shfl_any<int32_t>(s, pos);
       const int vv = (int)(ch * kWave) + pos;
       if (valid) {  // group-uniform
-        if (PHASE == kSpec && seq) {
+        if (seq) {
           // ready once every lower neighbour is final; then the least colour
           // absent from the final neighbours is the least absent from the
           // lower ones (a higher neighbour cannot be final before v)
@@ -447,20 +457,9 @@ __device__ void light_phase(const KArgs& a, long wave_gid, long nwaves, Tally& t
             const int t = spec_group<RP, S, L>(a.colidx, st, vb, ve, gl, 0);
             if (gl == 0) st[vv] = (S)~t;
           }
-        } else if (PHASE == kSpec) {
+        } else {
           int t = spec_group<RP, S, L>(a.colidx, st, vb, ve, gl, push ? kPushColors : 0);
           if (gl == 0) st[vv] = (S)~t;
-        } else {
-          // unsorted rows (sorted ones took the lane scan above): the whole
-          // row is scanned from its start
-          const int t = ~vs;
-          const bool lose = detect_group<RP, S, L>(a.colidx, st, vb, ve, vv, t, gl, gmask, false);
-          if (gl == 0) {
-            if (!lose) st[vv] = (S)t;
-            tl.lost += lose;
-            tl.cls |= (int)lose;
-          }
-          if (push && !lose) push_colour<RP, S>(a, st, vb, ve, t, epoch, gl, L);
         }
         if (gl == 0) tl.active += 1;
       }
