@@ -857,6 +857,16 @@ static bool use_resident(const gc_ctx* h) {
 // the passes takes 12 us at least, one of the core 6 to 8.
 constexpr int64_t kCoreMinRounds = 10;
 
+static int reserve_core(gc_ctx* h) {
+  if (h->core) return GC_OK;
+  const hipError_t e = hipMalloc(&h->core, gc::kCoreBytes);
+  if (e != hipSuccess) {
+    h->core = nullptr;
+    return set_err(h, GC_ENOMEM, "core pass: %s", hipGetErrorString(e));
+  }
+  return GC_OK;
+}
+
 // With R known, the round after which the core pass takes over: the first one
 // that leaves few enough vertices, if enough rounds follow.
 static int decide_core(gc_ctx* h) {
@@ -877,15 +887,15 @@ static int decide_core(gc_ctx* h) {
   }
   delete[] sizes;
   HIPCHECK(h, e);
+  // later calls allocate nothing; without room they run every round by its passes
+  if (h->core_round >= 0 && reserve_core(h)) h->core_round = -1;
   return GC_OK;
 }
 
 // The rounds after round0 as one core pass over at most `size` vertices.
 static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, hipStream_t s) {
-  if (!h->core) {
-    const hipError_t e = hipMalloc(&h->core, gc::kCoreBytes);
-    if (e != hipSuccess) return set_err(h, GC_ENOMEM, "core pass: %s", hipGetErrorString(e));
-  }
+  const int rc = reserve_core(h);
+  if (rc) return rc;
   gc::CoreArgs c;
   c.tents = (uint64_t*)h->core;
   c.wins = c.tents + gc::kCoreMax / 2;

@@ -14,7 +14,7 @@
 //          the uncoloured light ones and hands them to its 64/L groups in
 //          ascending order (an in-wave prefix sum over the ballot), so rows
 //          are read in address order and no global worklist or append
-//          atomics exist.
+//          atomics exist.  Conflict scans take one lane per vertex.
 //   medium light_max < deg < heavy threshold: one wavefront per vertex,
 //          from a static list built once per graph.
 //   heavy  one 256-thread workgroup per vertex, from a static list; its
