@@ -361,6 +361,10 @@ def graph_record(args, golden, host):
         scan2 = golden["sum_active_scan"] - (sizes[1] if len(sizes) > 1 else 0)
         push_rows = golden["push_rows_after_round1"]
 
+    # the p-block passes keep masks instead of slots within these limits
+    blk_masks = (algo == "blocks" and sbytes == 1
+                 and -(-g.n // golden["blocks_p"]) <= 256)
+
     def alg_bytes(sw):
         """(speculate, detect) bytes per colouring with each state access
         priced at sw bytes."""
@@ -373,27 +377,25 @@ def graph_record(args, golden, host):
         if algo == "push":
             det_b += push_rows * (4 + sw) + golden["push_useful_after_round1"]
         if algo == "seq":
-            # pick (speculate kernel), rounds 2..R: per visit the rowptr pair
-            # and the vertex's state; per waiting visit at least one
-            # lower-neighbour entry and its state; per vertex coloured, its row
-            # once (entry + state gather) and the state write.  Commit (detect
-            # kernel): per visit a state read, per vertex coloured a state
-            # write.
-            sv = golden["seq_visits_after_round1"]
-            sc = golden["seq_coloured_after_round1"]
-            spec_b = (sv * (2 * rp_b + sw) + golden["seq_waiting_visits_after_round1"]
-                      * (4 + sw) + golden["seq_rows_after_round1"] * (4 + sw) + sc * sw)
-            det_b = sv * sw + sc * sw
+            # one data-flow pass (timed as a speculate): every vertex's rowptr
+            # pair and its word, every lower-neighbour entry (half of them)
+            # and that neighbour's word
+            spec_b = g.n * (2 * rp_b + 4) + g.nnz // 2 * 8
+            det_b = 0
         if algo == "blocks":
-            # phase 1 ("speculate"): per pending vertex its rowptr pair, todo
-            # byte and colour write, per row entry the neighbour id and its
-            # slot or colour; phase 2 ("detect"): the same reads, per entry
-            # also the slot write (entries whose neighbour is in another
-            # block: all but ~0.2% at p = 16384), per pending vertex the todo
-            # write
             sa, sd = golden["blocks_sum_active"], golden["blocks_sum_active_deg"]
-            spec_b = sd * 8 + sa * (2 * rp_b + 1 + 4)
-            det_b = sd * 12 + sa * (2 * rp_b + 1 + 4 + 1)
+            if blk_masks:
+                # phase 1 ("speculate"): per pending vertex its todo byte, mask,
+                # in-block bits and colour; phase 2 ("detect"): per entry the
+                # neighbour id and its colour, per pending vertex the rowptr
+                # pair, todo byte and colour, and the mask it leaves
+                spec_b = sa * (1 + 16 + 8 + 2)
+                det_b = sd * 5 + sa * (2 * rp_b + 2 + 1 + 16)
+            else:
+                # with a slot per entry: phase 1 reads the neighbour id and its
+                # slot or colour, phase 2 also writes the slot
+                spec_b = sd * 8 + sa * (2 * rp_b + 1 + 4)
+                det_b = sd * 12 + sa * (2 * rp_b + 1 + 4 + 1)
         return spec_b, det_b
 
     # The per-unit figures price every state access at the scope table's
@@ -404,14 +406,14 @@ def graph_record(args, golden, host):
     spec_bytes_sw, det_bytes_sw = alg_bytes(sbytes)
     # rounds whose kernels are timed per colouring (round 1 has its own launch
     # except in the p-block colouring)
-    timed_rounds = rounds if algo == "blocks" else rounds - 1
+    timed_rounds = rounds if algo == "blocks" else 1 if algo == "seq" else rounds - 1
     spec_ms, spec_launches = prof["speculate"]
     det_ms, det_launches = prof["detect"]
     kernel = "detect" if det_ms > spec_ms else "speculate"
     k_ms, k_launches, k_bytes = ((det_ms, det_launches, det_bytes) if kernel == "detect"
                                  else (spec_ms, spec_launches, spec_bytes))
     k_bytes_sw = det_bytes_sw if kernel == "detect" else spec_bytes_sw
-    calls = max(1, k_launches // max(1, timed_rounds))
+    calls = max(1, args.steps)
     achieved = k_bytes * calls / (k_ms / 1e3) / 1e9 if k_ms > 0 else None
     achieved_sw = k_bytes_sw * calls / (k_ms / 1e3) / 1e9 if k_ms > 0 else None
     setting = {"workload": args.workload, "algorithm": algo, "lanes": lanes,
@@ -419,8 +421,8 @@ def graph_record(args, golden, host):
     pmc = read_summary(f"{kernel}_{args.workload}_pmc.txt", setting)
     traffic = int(pmc["bytes_per_launch"]) if pmc and "bytes_per_launch" in pmc else None
     roofline = {
-        "kernel": ({"speculate": "k_blk_phase1", "detect": "k_blk_phase2"}[kernel]
-                   if algo == "blocks" else kernel),
+        "kernel": ({"speculate": "phase1", "detect": "phase2"}[kernel]
+                   if algo == "blocks" else "k_seq_flow" if algo == "seq" else kernel),
         "bound": "hbm",
         "achieved": round(achieved, 1) if achieved else None,
         "peak": HBM_PEAK_GBS,
@@ -576,13 +578,10 @@ def batched_block(args, golden, host, standalone):
     t_step = elapsed / steps
     ref_colors = colors.clone()
 
-    # HBM roofline of the batch kernel: colidx entries the rounds read
-    # (speculate: every neighbour of every uncoloured vertex of rounds >= 2;
-    # detect: the lower-id prefix, an upper bound because the scan stops at
-    # the first conflict) plus each uncoloured vertex's rowptr pair; the
-    # state is in LDS and is not HBM traffic.
-    alg = 4 * (golden["sum_active_deg"] - int(b.eoff[-1]) + golden["sum_active_lower_deg"]) \
-        + 8 * golden["sum_active"]
+    # HBM roofline of the batch kernel: what a launch cannot do without, every
+    # row read once (entries and row pointers) and every colour written once.
+    # The state and the colour masks are in LDS.
+    alg = 4 * int(b.eoff[-1]) + 8 * n
     achieved = alg / (kernel_ms / 1e3) / 1e9
     pmc = read_summary(f"batch_{BATCH_WORKLOAD}_pmc.txt")
     traffic = int(pmc["bytes_per_launch"]) if pmc and "bytes_per_launch" in pmc else None
