@@ -134,12 +134,13 @@ struct gc_ctx {
   int64_t starts_room = 0;
   int32_t* unit_part = nullptr; // device, kUnitGrid + 1: per-workgroup unit counts, the number of units
   bool units_ready = false;
+  bool flow_off = false;     // no room for them: SEQ runs by the rounds
 
   // core pass (gc_core.hip), decided from the graph alone
   void* core = nullptr;      // device, kCoreBytes, allocated on first use
-  bool core_off = false;     // it gave up on this graph
+  bool core_off = false;     // it gave up on this graph, or found no room
   uint64_t* res = nullptr;   // resident pass (gc_resident.hip): device, resident_bytes(n)
-  bool res_off = false;      // it gave up on this graph
+  bool res_off = false;      // it gave up on this graph, or found no room
   int64_t core_round = -1;   // with R known: the core follows this round (-1: no core)
   int64_t core_size = 0;     // and has so many vertices
 
@@ -566,7 +567,7 @@ static int ensure_order(gc_ctx* h, hipStream_t s) {
   h->built_order = GC_ORDER_NATURAL;
   h->lists_dirty = true;
   h->known_rounds = 0;
-  h->core_off = h->res_off = false;
+  h->core_off = h->res_off = h->flow_off = false;
   if (h->order == GC_ORDER_NATURAL) return GC_OK;
   if (h->m > INT32_MAX)
     return set_err(h, GC_ETOOBIG, "vertex order: more than 2^31 - 1 CSR entries");
@@ -597,6 +598,7 @@ static int permute_back(gc_ctx* h, const int32_t* coloured, int32_t* colors_out,
 // Algorithm 1 with p blocks by masks instead of slots (gc_blocks.hip): rounds
 // queued eight at a time, or all of them once their number is known, and a
 // flag read back after them.
+static int color_blocks(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStream_t s);
 static int color_blocks_masks(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStream_t s) {
   const int64_t p = partitions_of(h);
   const int64_t per_block = (h->n + p - 1) / p;  // vertices of a block at most
@@ -609,7 +611,12 @@ static int color_blocks_masks(gc_ctx* h, int32_t* colors_out, int32_t* user_out,
     h->bwords = 0;
     hipError_t e = hipMalloc((void**)&h->bmask, (size_t)(2 + words) * h->n * sizeof(uint64_t));
     if (e == hipSuccess && !h->btodo) e = hipMalloc((void**)&h->btodo, (size_t)h->n);
-    if (e != hipSuccess) return set_err(h, GC_ENOMEM, "block masks: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {  // on a sparse graph the slots need less
+      (void)hipGetLastError();
+      if (h->bmask) (void)hipFree(h->bmask);
+      h->bmask = nullptr;
+      return color_blocks(h, colors_out, user_out, s);
+    }
     h->bwords = words;
   }
   h->stats_ready = false;
@@ -687,8 +694,10 @@ static int color_blocks_masks(gc_ctx* h, int32_t* colors_out, int32_t* user_out,
 // each round (R <= p).
 static int color_blocks(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStream_t s) {
   int rc = GC_OK;
-  if (h->n > 0 && !h->bslot) {
-    hipError_t e = hipMalloc((void**)&h->bslot, (size_t)std::max<int64_t>(h->m, 1) * sizeof(int32_t));
+  if (h->n > 0 && (!h->bslot || !h->btodo)) {
+    hipError_t e = hipSuccess;
+    if (!h->bslot)
+      e = hipMalloc((void**)&h->bslot, (size_t)std::max<int64_t>(h->m, 1) * sizeof(int32_t));
     if (e == hipSuccess && !h->btodo) e = hipMalloc((void**)&h->btodo, (size_t)h->n);
     if (e != hipSuccess) return set_err(h, GC_ENOMEM, "block slots: %s", hipGetErrorString(e));
   }
@@ -791,7 +800,15 @@ static int color_flow(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStre
     if (e == hipSuccess) e = hipMalloc((void**)&h->starts, (size_t)room * sizeof(int32_t));
     if (e == hipSuccess)
       e = hipMalloc((void**)&h->unit_part, (gc::kUnitGrid + 1) * sizeof(int32_t));
-    if (e != hipSuccess) return set_err(h, GC_ENOMEM, "data-flow words: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {  // the rounds need none of it
+      (void)hipGetLastError();
+      for (void* p : {h->word, (void*)h->starts, (void*)h->unit_part})
+        if (p) (void)hipFree(p);
+      h->word = nullptr;
+      h->starts = h->unit_part = nullptr;
+      h->flow_off = true;
+      return gc_color(h, user_out, s);
+    }
     h->word_bytes = wb;
     h->starts_room = room;
   }
@@ -857,14 +874,21 @@ static bool use_resident(const gc_ctx* h) {
 // the passes takes 12 us at least, one of the core 6 to 8.
 constexpr int64_t kCoreMinRounds = 10;
 
-static int reserve_core(gc_ctx* h) {
-  if (h->core) return GC_OK;
-  const hipError_t e = hipMalloc(&h->core, gc::kCoreBytes);
-  if (e != hipSuccess) {
-    h->core = nullptr;
-    return set_err(h, GC_ENOMEM, "core pass: %s", hipGetErrorString(e));
-  }
-  return GC_OK;
+// The passes' scratch, allocated once per handle; without room for it the
+// rounds run by their own passes.
+static bool reserve_core(gc_ctx* h) {
+  if (h->core || hipMalloc(&h->core, gc::kCoreBytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  h->core = nullptr;
+  h->core_off = true;
+  return false;
+}
+static bool reserve_resident(gc_ctx* h) {
+  if (h->res || hipMalloc((void**)&h->res, gc::resident_bytes(h->n)) == hipSuccess) return true;
+  (void)hipGetLastError();
+  h->res = nullptr;
+  h->res_off = true;
+  return false;
 }
 
 // With R known, the round after which the core pass takes over: the first one
@@ -887,15 +911,12 @@ static int decide_core(gc_ctx* h) {
   }
   delete[] sizes;
   HIPCHECK(h, e);
-  // later calls allocate nothing; without room they run every round by its passes
-  if (h->core_round >= 0 && reserve_core(h)) h->core_round = -1;
+  if (h->core_round >= 0 && !reserve_core(h)) h->core_round = -1;  // (later calls allocate nothing)
   return GC_OK;
 }
 
 // The rounds after round0 as one core pass over at most `size` vertices.
 static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, hipStream_t s) {
-  const int rc = reserve_core(h);
-  if (rc) return rc;
   gc::CoreArgs c;
   c.tents = (uint64_t*)h->core;
   c.wins = c.tents + gc::kCoreMax / 2;
@@ -910,10 +931,6 @@ static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, hipSt
 
 // The whole colouring in one resident pass.
 static int color_resident(gc_ctx* h, const KArgs& a, hipStream_t s) {
-  if (!h->res) {
-    const hipError_t e = hipMalloc((void**)&h->res, gc::resident_bytes(h->n));
-    if (e != hipSuccess) return set_err(h, GC_ENOMEM, "resident pass: %s", hipGetErrorString(e));
-  }
   LCHECK(h, gc::launch_resident(a, h->rp64, gc::ResArgs{h->res}, (int)h->known_rounds, s));
   return GC_OK;
 }
@@ -952,10 +969,10 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
     return masks ? color_blocks_masks(h, colors_out, user_out, s)
                  : color_blocks(h, colors_out, user_out, s);
   }
-  if (use_seq(h) && h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH)
+  if (use_seq(h) && h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH && !h->flow_off)
     return color_flow(h, colors_out, user_out, s);
-  const bool resident = use_resident(h);
-  const bool all_core = !resident && may_use_core(h) && h->n <= gc::kCoreMax;
+  const bool resident = use_resident(h) && reserve_resident(h);
+  const bool all_core = !resident && may_use_core(h) && h->n <= gc::kCoreMax && reserve_core(h);
   if (use_push(h) && !all_core && !resident) {
     if (!h->seen && h->n > 0) {
       const size_t nv = (size_t)(h->n + gc::kWave - 1) / gc::kWave * gc::kWave;  // whole chunks
@@ -1069,7 +1086,7 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
           HIPCHECK(h, hipStreamSynchronize(s));
           if (!h->host->fin[0]) break;
           if (h->max_rounds > 0 && r >= h->max_rounds) break;
-          if (may_use_core(h) && h->host->fin[1] <= gc::kCoreMax) {
+          if (may_use_core(h) && h->host->fin[1] <= gc::kCoreMax && reserve_core(h)) {
             rc = color_core(h, a, r, h->host->fin[1], s);
             if (rc) return rc;
             fused = true;
