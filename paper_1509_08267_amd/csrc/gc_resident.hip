@@ -13,10 +13,13 @@
 // Round 1 starts with detect: every vertex tries colour 0.  Every published
 // word carries its round, so that a reader polls the data itself.  Words
 // without an uncoloured vertex are neither published nor read (all replicas
-// agree on what is final), and a workgroup whose vertices are all coloured
-// leaves.  The workgroups that stay all publish something in each exchange,
-// so a word is rewritten only after everybody who reads it has published the
-// other kind in between: one buffer of each suffices.
+// agree on what is final).  A workgroup whose last vertices win leaves as soon
+// as it has published them, and reads nothing more: nobody waits for it from
+// then on, so a word that it still meant to read could be overwritten by the
+// next round's.  Everybody who reads the winners has vertices left and
+// publishes their states afterwards, and everybody who reads the states
+// publishes winners afterwards, so a word is rewritten only after all its
+// readers have read it: one buffer of each suffices.
 //
 // Bound by the two exchanges and the workgroup barriers around them, 7 us a
 // round.  Whole calls, uniform random graphs, before and after: 4,000 vertices
@@ -107,7 +110,7 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
   extern __shared__ __align__(16) char smem[];
   __shared__ int base[kResMaxChunks + 1];  // entry where each own chunk's rows start
   __shared__ uint32_t own_win[2 * kResMaxChunks];
-  __shared__ int sum, own_left;
+  __shared__ int sum;
   const ResLayout lay(a.n, gridDim.x, lds);
   int8_t* const st = (int8_t*)smem;
   int32_t* const off = (int32_t*)(smem + lay.chunks * kWave);
@@ -146,6 +149,8 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
     for (int i = tid; i < len; i += kResBlock) ent[base[ch] + i] = (uint16_t)a.colidx[from + i];
   }
   int left = a.n;  // uncoloured vertices of the graph
+  int own = 0;     // and of this workgroup
+  for (int i = 0; i < mine; ++i) own += min(kWave, a.n - (g + i * P) * kWave);
   int rounds = 0;
   const int gl = lane & (kResLanes - 1);
   const uint64_t gmask = ((1ull << kResLanes) - 1) << (lane & ~(kResLanes - 1));
@@ -153,7 +158,6 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
     for (int i = tid; i < 2 * mine; i += kResBlock) own_win[i] = 0;
     if (tid == 0) {
       sum = 0;
-      own_left = 0;
       const int rd = rounds + 1;
       if (rd <= kTraceRounds) a.ctrl->trace[rd - 1] = left;  // (the same from every workgroup)
     }
@@ -189,6 +193,8 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
       const int w = 2 * (g + (i / 2) * P) + (i & 1);
       if (open32(w)) publish(&wins[w], q, own_win[i]);
     }
+    for (int i = 0; i < 2 * mine; ++i) own -= __popc(own_win[i]);
+    if (own == 0) break;  // workgroup-uniform, and before anything is polled
     __syncthreads();  // (all words of st are looked at before any changes)
     int bad = 0, won = 0;
     for (int w0 = tid; w0 < 2 * lay.chunks; w0 += 2 * kResBlock) {
@@ -216,7 +222,6 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
     if (__syncthreads_or(bad)) return;
     left -= sum;
     // speculate: own vertices still uncoloured
-    int some = 0;
     for (int i0 = 0; i0 < mine * kWave; i0 += kResBlock / kResLanes) {
       const int i = i0 + tid / kResLanes;
       const int ch = i / kWave, v = i < mine * kWave ? (g + ch * P) * kWave + i % kWave : 0;
@@ -236,12 +241,10 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
         // (own uncoloured states are read by their own group alone here)
         if (act && gl == 0)
           st[v] = (int8_t)~(~lo ? __builtin_ctzll(~lo) : 64 + __builtin_ctzll(~hi));
-        some |= act;
       }
     }
-    if (some) own_left = 1;
     __syncthreads();
-    if (!own_left || (last > 0 && rounds >= last)) break;
+    if (last > 0 && rounds >= last) break;
     // states: words with an uncoloured vertex
     auto open6 = [&](int ch, int j) {
       bool o = false;
@@ -283,7 +286,8 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
     if (__syncthreads_or(bad)) return;
   }
   if (tid == 0) atomicMax(&a.ctrl->last_round.v, rounds);
-  // (a bounded run: what is left stays uncoloured)
+  if (own == 0) return;
+  // a bounded run: what is left stays uncoloured
   for (int i = tid; i < mine * kWave; i += kResBlock) {
     const int v = (g + (i / kWave) * P) * kWave + i % kWave;
     if (v < a.n && st[v] < 0) ((int8_t*)a.st)[v] = st[v];
