@@ -115,7 +115,9 @@ int gc_create(gc_handle *out, const void *rowptr, const int32_t *colidx,
  *   stream      all work is queued here.  The first call on a handle reads a
  *               4-byte flag back every few rounds to find the round count R;
  *               later calls queue all R rounds and return at once (R depends
- *               on the graph only).  GC_MODE_HOST reads back every round.
+ *               on the graph only), but for the first one that colours a
+ *               small graph in one launch after R was learned in another mode:
+ *               it waits as well.  GC_MODE_HOST reads back every round.
  *
  * Calls on one handle are ordered: a call queued while the previous one is
  * still running (on any stream) first waits for it on the device, since both

@@ -121,6 +121,7 @@ struct gc_ctx {
   bool in_flight = false;
   bool stats_ready = false;
   int64_t known_rounds = 0;  // R of this graph once a call has completed (0 = unknown)
+  int32_t known_colors = 0;  // and the colours of that call
   int64_t partitions = 0;    // p of GC_ALGO_BLOCKS (0 = auto)
   int32_t* bslot = nullptr;  // device, nnz: ForbiddenColors slots (GC_ALGO_BLOCKS)
   uint8_t* btodo = nullptr;  // device, n
@@ -141,6 +142,7 @@ struct gc_ctx {
   bool core_off = false;     // it gave up on this graph, or found no room
   uint64_t* res = nullptr;   // resident pass (gc_resident.hip): device, resident_bytes(n)
   bool res_off = false;      // it gave up on this graph, or found no room
+  bool res_ok = false;       // it has coloured this graph
   int64_t core_round = -1;   // with R known: the core follows this round (-1: no core)
   int64_t core_size = 0;     // and has so many vertices
 
@@ -567,7 +569,7 @@ static int ensure_order(gc_ctx* h, hipStream_t s) {
   h->built_order = GC_ORDER_NATURAL;
   h->lists_dirty = true;
   h->known_rounds = 0;
-  h->core_off = h->res_off = h->flow_off = false;
+  h->core_off = h->res_off = h->res_ok = h->flow_off = false;
   if (h->order == GC_ORDER_NATURAL) return GC_OK;
   if (h->m > INT32_MAX)
     return set_err(h, GC_ETOOBIG, "vertex order: more than 2^31 - 1 CSR entries");
@@ -863,7 +865,13 @@ static bool may_fuse_rounds(const gc_ctx* h) {
   return h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH && h->max_rounds == 0 && !use_seq(h) &&
          h->algorithm != GC_ALGO_BLOCKS && !h->profile;
 }
-static bool may_use_core(const gc_ctx* h) { return may_fuse_rounds(h) && !h->core_off; }
+// The core pass gives up where a vertex finds all its kCoreColors colours taken, which is where
+// the colouring has more of them (a tentative colour never exceeds the final one): with R known,
+// so are the colours.
+static bool may_use_core(const gc_ctx* h) {
+  return may_fuse_rounds(h) && !h->core_off &&
+         (h->known_rounds == 0 || h->known_colors <= gc::kCoreColors);
+}
 static bool use_resident(const gc_ctx* h) {
   return may_fuse_rounds(h) && !h->res_off && gc::resident_fits(h->n, h->m, h->sbytes);
 }
@@ -1110,12 +1118,15 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));
   LCHECK(h, gc::launch_finish(a, h->sbytes, h->fin_dev, s));
-  if (fused && h->known_rounds == 0) {
+  // Whether the pass can run on this graph: looked at once, with or without R known (the rows of a
+  // workgroup may not fit the resident pass; for the core pass see may_use_core).
+  if (fused && (h->known_rounds == 0 || (resident && !h->res_ok))) {
     HIPCHECK(h, hipStreamSynchronize(s));
     if (h->host->fin[4]) {  // once per graph: again, by the rounds' own passes
       (resident ? h->res_off : h->core_off) = true;
       return gc_color(h, user_out, stream);
     }
+    if (resident) h->res_ok = true;
   }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[3], s));
   h->pending_profile = h->profile && mode != GC_MODE_PERSISTENT;
@@ -1162,6 +1173,7 @@ static int wait_done(gc_ctx* h) {
   }
   if (h->max_rounds == 0 && h->known_rounds != h->host->last_round) {
     h->known_rounds = h->host->last_round;
+    h->known_colors = h->host->ncolors;
     return decide_core(h);
   }
   return GC_OK;

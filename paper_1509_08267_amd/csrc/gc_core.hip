@@ -52,7 +52,6 @@ constexpr int kCoreBlock = 1024;
 constexpr int kCoreWaves = kCoreBlock / kWave;
 constexpr int kCoreWords = kCoreMax / kWave;  // 64-bit words of a matrix row at most
 constexpr int kCorePitch = kCoreWords + 1;    // (padded: equal words of 64 rows on all banks)
-constexpr int kCoreColors = 512;
 constexpr int kMaskPitch = kCoreColors / 32 + 1;
 constexpr int kNoTent = 0x3ff;   // published by a final vertex (or past the last one)
 constexpr int kGaveUp = 0x3fe;   // published by a vertex with all 512 colours taken

@@ -133,6 +133,7 @@ struct KArgs {
 
 // Scratch of the core pass (gc_core.hip).
 constexpr int kCoreMax = 4096;  // core vertices at most
+constexpr int kCoreColors = 512;  // colours with a mask bit: beyond them the pass gives up
 constexpr int kCoreGrid = 256;  // workgroups of the collecting pass at most
 struct CoreArgs {
   int32_t* ids;      // kCoreMax: the core vertices in id order
