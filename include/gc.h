@@ -178,7 +178,15 @@ enum gc_option {
   GC_OPT_ALGORITHM = 14,     /* enum gc_algorithm (default GC_ALGO_AUTO)           */
   GC_OPT_PARTITIONS = 15,    /* p for GC_ALGO_BLOCKS; 0 = auto (64 per compute unit) */
   GC_OPT_ORDER = 16,         /* enum gc_order (default GC_ORDER_NATURAL)            */
-  GC_OPT_ORDER_SEED = 17     /* seed of GC_ORDER_RANDOM (default 0)                 */
+  GC_OPT_ORDER_SEED = 17,    /* seed of GC_ORDER_RANDOM (default 0)                 */
+  GC_OPT_WAIT_POLLS = 18     /* The default driver runs a small graph, or the last
+                                rounds of a large one, in one launch of up to 64
+                                workgroups that wait for each other (eight such
+                                launches fit the GPU together).  A wait gives up
+                                after this many polls (2^20, about a second), and
+                                the vertices are coloured without it; 0: no such
+                                launches.  Reads 0 once the handle has stopped
+                                using one; setting it lets it try again      */
 };
 /* The vertex order the colouring follows (the paper's future work names
  * ordering schemes; its related work, Jones and Plassmann's random order).

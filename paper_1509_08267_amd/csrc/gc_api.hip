@@ -145,6 +145,8 @@ struct gc_ctx {
   bool res_ok = false;       // it has coloured this graph
   int64_t core_round = -1;   // with R known: the core follows this round (-1: no core)
   int64_t core_size = 0;     // and has so many vertices
+  int wait_polls = 1 << 20;  // polls after which a wait in them gives up (about a second); 0: unused
+  enum { kNone, kRes, kCore } fused = kNone;  // the pass that the last call took
 
   Captured exact;  // R - 1 rounds, once R is known
 
@@ -863,7 +865,7 @@ static int color_flow(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStre
 // core pass, or all of them in the resident pass.
 static bool may_fuse_rounds(const gc_ctx* h) {
   return h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH && h->max_rounds == 0 && !use_seq(h) &&
-         h->algorithm != GC_ALGO_BLOCKS && !h->profile;
+         h->algorithm != GC_ALGO_BLOCKS && !h->profile && h->wait_polls > 0;
 }
 // The core pass gives up where a vertex finds all its kCoreColors colours taken, which is where
 // the colouring has more of them (a tentative colour never exceeds the final one): with R known,
@@ -924,8 +926,10 @@ static int decide_core(gc_ctx* h) {
 }
 
 // The rounds after round0 as one core pass over at most `size` vertices.
-static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, hipStream_t s) {
+static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, gc::AloneArgs* w,
+                      hipStream_t s) {
   gc::CoreArgs c;
+  c.polls = h->wait_polls;
   c.tents = (uint64_t*)h->core;
   c.wins = c.tents + gc::kCoreMax / 2;
   c.ids = (int32_t*)(c.wins + 2 * (gc::kCoreMax / 64));
@@ -934,13 +938,31 @@ static int color_core(gc_ctx* h, const KArgs& a, int round0, int64_t size, hipSt
   const int workgroups = (int)((size + gc::kWave - 1) / gc::kWave);
   // (no round beyond the known ones: a graph that was changed is reported)
   LCHECK(h, gc::launch_core(a, h->rp64, h->sbytes, c, round0, (int)h->known_rounds, workgroups, s));
+  *w = {c.ids, round0, (int)h->known_rounds, h->rp64};
+  h->fused = gc_ctx::kCore;
   return GC_OK;
 }
 
 // The whole colouring in one resident pass.
-static int color_resident(gc_ctx* h, const KArgs& a, hipStream_t s) {
-  LCHECK(h, gc::launch_resident(a, h->rp64, gc::ResArgs{h->res}, (int)h->known_rounds, s));
+static int color_resident(gc_ctx* h, const KArgs& a, gc::AloneArgs* w, hipStream_t s) {
+  const gc::ResArgs r{h->res, h->wait_polls};
+  LCHECK(h, gc::launch_resident(a, h->rp64, r, (int)h->known_rounds, s));
+  *w = {nullptr, 0, (int)h->known_rounds, h->rp64};
+  h->fused = gc_ctx::kRes;
   return GC_OK;
+}
+
+// The last call's pass is not taken again on this graph.
+static void drop_fused(gc_ctx* h) {
+  if (h->fused == gc_ctx::kRes) h->res_off = true;
+  if (h->fused == gc_ctx::kCore) h->core_off = true;
+  h->fused = gc_ctx::kNone;
+}
+// The same once the finishing kernel reports that it had to colour in its place.
+static void drop_recoloured(gc_ctx* h) {
+  if (h->fused != gc_ctx::kNone &&
+      __atomic_load_n(&h->host->fin[4], __ATOMIC_RELAXED) == gc::kRecoloured)
+    drop_fused(h);
 }
 
 extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
@@ -971,6 +993,8 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
     if (rc) return rc;
   }
   (void)hipGetLastError();  // launch checks below must see only this call's errors
+  drop_recoloured(h);
+  h->fused = gc_ctx::kNone;
   if (h->algorithm == GC_ALGO_BLOCKS) {
     const bool masks = h->n > 0 && h->sbytes == 1 &&
                        (h->n + partitions_of(h) - 1) / partitions_of(h) <= gc::kBlkMaxVertices;
@@ -1026,16 +1050,16 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   KArgs a = make_args(h, colors_out, light);
   const int grid = round_grid(h);
   const int mode = resolve_mode(h);
-  bool fused = resident || all_core;  // the core or the resident pass has been queued
+  gc::AloneArgs w{};  // of the core or resident pass, once queued
 
-  if (fused) a.push = 0;  // (no flags to clear)
+  if (resident || all_core) a.push = 0;  // (no flags to clear)
   LCHECK(h, gc::launch_init(a, s));
   if (resident) {
-    rc = color_resident(h, a, s);
+    rc = color_resident(h, a, &w, s);
     if (rc) return rc;
   } else if (all_core) {
     LCHECK(h, gc::launch_fill_tent0(a, h->sbytes, grid, s));
-    rc = color_core(h, a, 0, h->n, s);
+    rc = color_core(h, a, 0, h->n, &w, s);
     if (rc) return rc;
   } else if (mode == GC_MODE_PERSISTENT) {
     int maxg = 0;
@@ -1080,9 +1104,8 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
         HIPCHECK(h, hipGraphLaunch(h->exact.exec, s));
       }
       if (core) {
-        rc = color_core(h, a, (int)h->core_round, h->core_size, s);
+        rc = color_core(h, a, (int)h->core_round, h->core_size, &w, s);
         if (rc) return rc;
-        fused = true;
       }
     } else {
       const int K = std::max(1, h->chunk_rounds);
@@ -1095,9 +1118,8 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
           if (!h->host->fin[0]) break;
           if (h->max_rounds > 0 && r >= h->max_rounds) break;
           if (may_use_core(h) && h->host->fin[1] <= gc::kCoreMax && reserve_core(h)) {
-            rc = color_core(h, a, r, h->host->fin[1], s);
+            rc = color_core(h, a, r, h->host->fin[1], &w, s);
             if (rc) return rc;
-            fused = true;
             break;
           }
         }
@@ -1117,13 +1139,19 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
     }
   }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));
-  LCHECK(h, gc::launch_finish(a, h->sbytes, h->fin_dev, s));
   // Whether the pass can run on this graph: looked at once, with or without R known (the rows of a
-  // workgroup may not fit the resident pass; for the core pass see may_use_core).
-  if (fused && (h->known_rounds == 0 || (resident && !h->res_ok))) {
+  // workgroup may not fit the resident pass; for the core pass see may_use_core).  A wait that gave
+  // up is looked at as well; in calls that nobody looks at the finishing kernel makes up for it.
+  const bool check = h->fused != gc_ctx::kNone &&
+                     (h->known_rounds == 0 || (resident && !h->res_ok));
+  if (h->fused != gc_ctx::kNone && !check)
+    LCHECK(h, gc::launch_finish_fused(a, h->sbytes, w, h->fin_dev, s));
+  else
+    LCHECK(h, gc::launch_finish(a, h->sbytes, h->fin_dev, s));
+  if (check) {
     HIPCHECK(h, hipStreamSynchronize(s));
-    if (h->host->fin[4]) {  // once per graph: again, by the rounds' own passes
-      (resident ? h->res_off : h->core_off) = true;
+    if (h->host->fin[4] || h->host->fin[1]) {  // again, by the rounds' own passes
+      drop_fused(h);
       return gc_color(h, user_out, stream);
     }
     if (resident) h->res_ok = true;
@@ -1162,6 +1190,7 @@ static int wait_done(gc_ctx* h) {
     h->in_flight = false;
   }
   fold_finish(h);  // the call has completed (also when another path waited for it)
+  drop_recoloured(h);
   collect_profile(h);
   if (h->host->abort) return set_err(h, GC_EDEVICE, "a wait inside a kernel timed out");
   if (h->host->left) {
@@ -1268,6 +1297,11 @@ extern "C" int gc_set_option(gc_handle h, int option, int64_t value) {
       if (h->algorithm == GC_ALGO_BLOCKS) h->known_rounds = 0;
       h->partitions = value;
       return GC_OK;
+    case GC_OPT_WAIT_POLLS:
+      if (value < 0 || value > INT32_MAX) break;
+      h->wait_polls = (int)value;
+      h->core_off = h->res_off = false;
+      return GC_OK;
     case GC_OPT_PROFILE:
       if (value < 0 || value > 1) break;
       if (value && !h->pev[0]) {
@@ -1305,6 +1339,7 @@ extern "C" int gc_get_option(gc_handle h, int option, int64_t* value) {
                                               : GC_ALGO_PULL;
       return GC_OK;
     case GC_OPT_PARTITIONS: *value = partitions_of(h); return GC_OK;
+    case GC_OPT_WAIT_POLLS: *value = h->core_off || h->res_off ? 0 : h->wait_polls; return GC_OK;
     case GC_OPT_ORDER: *value = h->order; return GC_OK;
     case GC_OPT_ORDER_SEED: *value = (int64_t)h->order_seed; return GC_OK;
     default: return set_err(h, GC_EINVAL, "gc_get_option: unknown option %d", option);

@@ -24,9 +24,12 @@
 // one buffer of each suffices.  The words are relaxed agent-scope atomics.
 //
 // Every workgroup waits for all the others, so all of them have to be resident
-// together: at most 64 workgroups of about 80 KB, two to a compute unit, leave
-// room for the four kernels a process runs at once on its hardware queues and
-// more.  Every wait is bounded (abort flag), as in the persistent kernel.
+// together: at most 64 workgroups of about 80 KB, two to a compute unit, so that
+// eight such launches fit 256 compute units, more than the four kernels a process
+// runs at once on its hardware queues.  Several processes may have more, or other
+// kernels may keep the rest of a launch from starting for long: every wait is
+// bounded (abort flag), and the vertices of a pass that gave up are coloured by the
+// finishing kernel (color_alone).
 //
 // Bound by the two exchanges, about 2 us each. Measured, whole calls: R-MAT of
 // scale 22 (the last 202 of 315 rounds) 20.7 -> 15.9 ms, 8,000 vertices and 4 M
@@ -56,7 +59,6 @@ constexpr int kMaskPitch = kCoreColors / 32 + 1;
 constexpr int kNoTent = 0x3ff;   // published by a final vertex (or past the last one)
 constexpr int kGaveUp = 0x3fe;   // published by a vertex with all 512 colours taken
 constexpr int kLongRow = 8192;   // rows above this are built by the whole workgroup
-constexpr long kCoreSpinLimit = 1l << 25;
 
 struct CoreSmem {
   uint64_t rows[kWave][kCorePitch];
@@ -71,7 +73,8 @@ struct CoreSmem {
 };
 
 // Polls p until its high half carries `tag`; false when the wait was given up.
-__device__ __forceinline__ bool poll(const uint64_t* p, uint32_t tag, Ctrl* c, uint64_t* out) {
+__device__ __forceinline__ bool poll(const uint64_t* p, uint32_t tag, Ctrl* c, int polls,
+                                     uint64_t* out) {
   long spins = 0;
   for (;;) {
     const uint64_t x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -79,7 +82,7 @@ __device__ __forceinline__ bool poll(const uint64_t* p, uint32_t tag, Ctrl* c, u
       *out = x;
       return true;
     }
-    if (++spins > kCoreSpinLimit)
+    if (++spins > polls)
       __hip_atomic_store(&c->abort.v, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((spins & 1023) == 0 &&
         __hip_atomic_load(&c->abort.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
@@ -184,17 +187,17 @@ __global__ __launch_bounds__(kCoreBlock) void k_core(KArgs a, CoreArgs c, int ro
     int left = 0, bad = 0;
     for (int i = tid; i < nw * (kWave / 2); i += kCoreBlock) {
       uint64_t x = 0;
-      if (!poll(&c.tents[i], q, a.ctrl, &x)) bad = 1;
+      if (!poll(&c.tents[i], q, a.ctrl, c.polls, &x)) bad = 1;
       const int x0 = (int)(x & 0xffff), x1 = (int)((x >> 16) & 0xffff);
       sm.tent[2 * i] = (uint16_t)x0;
       sm.tent[2 * i + 1] = (uint16_t)x1;
       left += (x0 != kNoTent) + (x1 != kNoTent);
-      bad |= x0 == kGaveUp || x1 == kGaveUp;
+      if (x0 == kGaveUp || x1 == kGaveUp) {  // (every workgroup reads the same words)
+        a.ctrl->core_fail.v = 1;
+        bad = 1;
+      }
     }
-    if (__syncthreads_or(bad)) {
-      if (tid == 0) a.ctrl->core_fail.v = 1;
-      return;  // (the same in every workgroup: all read the same words)
-    }
+    if (__syncthreads_or(bad)) return;
     if (!__syncthreads_or(left) || (last > 0 && round0 + rounds >= last)) break;
     ++rounds;
     if (g == 0) {  // |U_r|, by workgroup 0
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(kCoreBlock) void k_core(KArgs a, CoreArgs c, int ro
     bad = 0;
     if (tid < 2 * nw) {
       uint64_t x = 0;
-      if (!poll(&c.wins[tid], q, a.ctrl, &x)) bad = 1;
+      if (!poll(&c.wins[tid], q, a.ctrl, c.polls, &x)) bad = 1;
       sm.win[tid] = (uint32_t)x;
     }
     if (__syncthreads_or(bad)) return;

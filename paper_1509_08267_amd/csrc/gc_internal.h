@@ -58,7 +58,7 @@ struct Ctrl {
   Line last_round;       // last round that had uncoloured vertices
   Line round_base;       // first round of the next captured chunk
   Line bar;              // grid barrier arrivals (monotonic within a launch)
-  Line abort;            // set when a barrier wait exceeded its spin limit
+  Line abort;            // set when a wait for other workgroups exceeded its limit
   Line left;             // vertices still uncoloured after the last round
   Line epoch;            // value marking this call's pushed colour flags (1..255)
   Line pend;             // round whose per-workgroup counts in KArgs::part are not yet in
@@ -140,6 +140,7 @@ struct CoreArgs {
   int32_t* part;     // kCoreGrid: uncoloured vertices per workgroup of the collecting pass
   uint64_t* tents;   // kCoreMax / 2: published tentative colours, round << 32 | two of them
   uint64_t* wins;    // 2 * kCoreMax / 64: published winners, round << 32 | 32 of them
+  int32_t polls;     // polls after which a wait gives up
 };
 constexpr size_t kCoreBytes = (size_t)kCoreMax * 4 + kCoreGrid * 4 + (size_t)kCoreMax / 2 * 8 +
                               (size_t)2 * (kCoreMax / 64) * 8;
@@ -156,6 +157,7 @@ constexpr int kResMaxChunks = 6;       // 64-vertex chunks of one at most: 24,57
 constexpr int kResLds = 78 * 1024;     // LDS of one (two to a compute unit)
 struct ResArgs {
   uint64_t* words;  // resident_bytes(n): the published words
+  int32_t polls;    // polls after which a wait gives up
 };
 size_t resident_bytes(int64_t n);
 // Whether a graph's rows (on average) and states fit; one-byte states only.
@@ -262,11 +264,24 @@ int launch_report(const KArgs& a, int round, int32_t* out, void* stream);
 // device-visible pinned host memory) receives, by system-scope stores:
 //   out[0] last round, out[1] abort flag, out[2] uncoloured count recorded by
 //   earlier passes (ctrl->left), out[3] workgroups G of this pass, out[4]
-//   whether the core or resident pass gave up, and for each workgroup b < G:
+//   whether the core or resident pass could not run, and for each workgroup b < G:
 //   out[5 + 2b] = its largest colour + 1 (0 if none), out[6 + 2b] = its
 //   uncoloured vertices.
 // The host folds them once the stream has passed this kernel.
 int launch_finish(const KArgs& a, int sbytes, int32_t* out, void* stream);
+
+// After a core or resident pass whose result nobody looks at before it is used:
+// when a wait in it gave up (ctrl->abort), the vertices it had are coloured again
+// by this kernel's first workgroup alone, which waits for nobody, and out[4] is
+// kRecoloured, out[1] 0.
+constexpr int kRecoloured = 2;
+struct AloneArgs {
+  const int32_t* ids;  // the ctrl->core_n vertices of a core pass in id order, or null: all
+  int32_t round0;      // the rounds start after it
+  int32_t last;        // and none follows `last` (0: no bound)
+  int32_t rp64;
+};
+int launch_finish_fused(const KArgs& a, int sbytes, const AloneArgs& w, int32_t* out, void* stream);
 int launch_persistent(const KArgs& a, bool rp64, int sbytes, int lanes, int max_rounds, int grid,
                       void* stream);
 int persistent_max_grid(bool rp64, int sbytes, int lanes, int* grid_out);

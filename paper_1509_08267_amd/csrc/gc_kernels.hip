@@ -1038,15 +1038,15 @@ __global__ __launch_bounds__(kBlock) void k_report(KArgs a, int round, int32_t* 
 // vertices): one 16-byte load, and 16-byte stores when both arrays are
 // 16-byte aligned (VEC).  No device atomics: the host folds the
 // per-workgroup pairs.
+// `alone`: the first workgroup takes all vertices.
 template <typename S, bool VEC>
-__global__ __launch_bounds__(kBlock) void k_finish(KArgs a, int32_t* out) {
+__device__ __forceinline__ void finish(const KArgs& a, int32_t* out, bool alone) {
   __shared__ int sh_max[kWavesPerBlock], sh_left[kWavesPerBlock];
-  if (blockIdx.x == 0) fold_trace(a.ctrl, a.part);  // the last detect pass's round size
   constexpr int V = 16 / (int)sizeof(S);
   const S* __restrict__ st = (const S*)a.st;
   int mx = -1, left = 0;
-  const long nth = (long)gridDim.x * blockDim.x;
-  const long ngroups = ((long)a.n + V - 1) / V;
+  const long nth = (alone ? 1l : (long)gridDim.x) * blockDim.x;
+  const long ngroups = alone && blockIdx.x > 0 ? 0 : ((long)a.n + V - 1) / V;
   for (long g = blockIdx.x * (long)blockDim.x + threadIdx.x; g < ngroups; g += nth) {
     const long v0 = g * V;
     int s[V];
@@ -1093,12 +1093,85 @@ __global__ __launch_bounds__(kBlock) void k_finish(KArgs a, int32_t* out) {
     store_system(&out[kFinishHeader + 1 + 2 * blockIdx.x], left);
     if (blockIdx.x == 0) {
       store_system(&out[0], a.ctrl->last_round.v);
-      store_system(&out[1], a.ctrl->abort.v);
+      store_system(&out[1], alone ? 0 : a.ctrl->abort.v);
       store_system(&out[2], a.ctrl->left.v);
       store_system(&out[3], (int32_t)gridDim.x);
-      store_system(&out[4], a.ctrl->core_fail.v);
+      store_system(&out[4], alone ? kRecoloured : a.ctrl->core_fail.v);
     }
   }
+}
+
+template <typename S, bool VEC>
+__global__ __launch_bounds__(kBlock) void k_finish(KArgs a, int32_t* out) {
+  if (blockIdx.x == 0) fold_trace(a.ctrl, a.part);  // the last detect pass's round size
+  finish<S, VEC>(a, out, false);
+}
+
+// The rounds of w's vertices by one workgroup, a wavefront per vertex: slow, but
+// without a wait for any other workgroup.  The pass that gave up may have left
+// some of them coloured: they start over, which gives the same colours.
+template <typename RP, typename S>
+__device__ void color_alone(const KArgs& a, const AloneArgs& w) {
+  __shared__ int sh[kWavesPerBlock];
+  const RP* rp = (const RP*)a.rowptr;
+  S* const st = (S*)a.st;
+  const int N = w.ids ? a.ctrl->core_n.v : a.n;
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
+  auto id = [&](int i) { return w.ids ? w.ids[i] : i; };
+  for (int i = threadIdx.x; i < N; i += kBlock) st[id(i)] = (S)-1;
+  __syncthreads();
+  // f(v, s) of every uncoloured vertex and its state, a wavefront's own 64 at a time
+  auto each_open = [&](auto f) {
+    int count = 0;
+    for (int c0 = wave * kWave; c0 < N; c0 += kBlock) {
+      const int mine = c0 + lane < N ? id(c0 + lane) : 0;
+      const int s = c0 + lane < N ? (int)st[mine] : 0;
+      uint64_t m = __ballot(s < 0);
+      count += __popcll(m);
+      while (m) {  // wave-uniform
+        const int i = __builtin_ctzll(m);
+        m &= m - 1;
+        f(__shfl(mine, i), __shfl(s, i));
+      }
+    }
+    return count;
+  };
+  int r = w.round0;
+  for (;;) {
+    const int mine = each_open([&](int v, int) {
+      const int t = spec_group<RP, S, kWave>(a.colidx, st, rp[v], rp[v + 1], lane);
+      if (lane == 0) st[v] = (S)~t;
+    });
+    if (lane == 0) sh[wave] = mine;
+    __syncthreads();
+    int left = 0;
+    for (int q = 0; q < kWavesPerBlock; ++q) left += sh[q];
+    // (every round colours the lowest uncoloured vertex: at most N of them)
+    if (left == 0 || (w.last > 0 && r >= w.last)) break;
+    ++r;
+    if (threadIdx.x == 0) {
+      if (r <= kTraceRounds) a.ctrl->trace[r - 1] = left;
+      a.ctrl->last_round.v = r;
+    }
+    each_open([&](int v, int s) {
+      const bool lose = detect_group<RP, S, kWave>(a.colidx, st, rp[v], rp[v + 1], v, ~s, lane,
+                                                   ~0ull, false);
+      if (lane == 0 && !lose) st[v] = (S)~s;
+    });
+    __syncthreads();
+  }
+}
+
+// The finishing pass behind a core or resident pass (see launch_finish_fused).
+template <typename S, bool VEC>
+__global__ __launch_bounds__(kBlock) void k_finish_fused(KArgs a, AloneArgs w, int32_t* out) {
+  const bool alone = a.ctrl->abort.v != 0;
+  if (alone && blockIdx.x == 0) {
+    if (w.rp64) color_alone<int64_t, S>(a, w);
+    else color_alone<int32_t, S>(a, w);
+    __syncthreads();
+  }
+  finish<S, VEC>(a, out, alone);
 }
 
 // Grid-wide barrier of a co-resident (cooperative) grid.  Arrivals count up
@@ -1388,21 +1461,41 @@ int launch_report(const KArgs& a, int round, int32_t* out, void* stream) {
   return (int)hipGetLastError();
 }
 
-int launch_finish(const KArgs& a, int sbytes, int32_t* out, void* stream) {
-  hipStream_t s = (hipStream_t)stream;
+static int launch_finish_of(const KArgs& a, int sbytes, const AloneArgs* w, int32_t* out,
+                            hipStream_t s) {
   if (sbytes != 1 && sbytes != 2 && sbytes != 4) return (int)hipErrorInvalidValue;
   // 16 bytes of state per thread, at most kFinishBlocks workgroups
   const long per = (16l / sbytes) * kBlock;
   const int grid = (int)std::max<long>(1, std::min<long>(kFinishBlocks, ((long)a.n + per - 1) / per));
   const bool vec = ((uintptr_t)a.st % 16 == 0) && ((uintptr_t)a.colors % 16 == 0);
-#define GC_FINISH(S_)                                                                     \
-  if (vec) hipLaunchKernelGGL((k_finish<S_, true>), dim3(grid), dim3(kBlock), 0, s, a, out); \
-  else hipLaunchKernelGGL((k_finish<S_, false>), dim3(grid), dim3(kBlock), 0, s, a, out)
-  if (sbytes == 1) GC_FINISH(int8_t);
-  else if (sbytes == 2) GC_FINISH(int16_t);
-  else GC_FINISH(int32_t);
+#define GC_FINISH(S_, VEC_)                                                                   \
+  if (w) hipLaunchKernelGGL((k_finish_fused<S_, VEC_>), dim3(grid), dim3(kBlock), 0, s, a, *w, out); \
+  else hipLaunchKernelGGL((k_finish<S_, VEC_>), dim3(grid), dim3(kBlock), 0, s, a, out)
+#define GC_FINISH_VEC(S_)    \
+  if (vec) {                 \
+    GC_FINISH(S_, true);     \
+  } else {                   \
+    GC_FINISH(S_, false);    \
+  }
+  if (sbytes == 1) {
+    GC_FINISH_VEC(int8_t)
+  } else if (sbytes == 2) {
+    GC_FINISH_VEC(int16_t)
+  } else {
+    GC_FINISH_VEC(int32_t)
+  }
+#undef GC_FINISH_VEC
 #undef GC_FINISH
   return (int)hipGetLastError();
+}
+
+int launch_finish(const KArgs& a, int sbytes, int32_t* out, void* stream) {
+  return launch_finish_of(a, sbytes, nullptr, out, (hipStream_t)stream);
+}
+
+int launch_finish_fused(const KArgs& a, int sbytes, const AloneArgs& w, int32_t* out,
+                        void* stream) {
+  return launch_finish_of(a, sbytes, &w, out, (hipStream_t)stream);
 }
 
 int launch_classify(const void* rowptr, bool rp64, int32_t n, int32_t light_max, int32_t heavy_min,

@@ -28,8 +28,8 @@
 // 40,000 of 8 the rounds' own passes are ahead (116 against 140), as every
 // workgroup reads every vertex's state, so the pass ends at 24,576 vertices.
 //
-// As in the core pass every workgroup waits for the others: at most 64
-// workgroups of at most 80 KB, all resident together, and bounded waits.
+// As in the core pass the workgroups wait for each other: at most 64 of at most
+// 80 KB, and bounded waits, after which the finishing kernel colours the graph.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -46,7 +46,6 @@ constexpr int kResBlock = 1024;
 constexpr int kPack = 6;                            // states to a word
 constexpr int kChunkWords = (kWave + kPack - 1) / kPack;
 constexpr int kResLanes = 8;                        // lanes per own vertex
-constexpr long kResSpinLimit = 1l << 25;
 
 // LDS layout: the states of every vertex (whole chunks), the own rows' entries,
 // and per own vertex the start of its row.
@@ -63,7 +62,7 @@ struct ResLayout {
 // flight together; false when the wait was given up.
 template <int K>
 __device__ __forceinline__ bool poll_words(const uint64_t* p, const int* i, uint32_t want,
-                                           uint32_t tag, Ctrl* c, uint64_t* x) {
+                                           uint32_t tag, Ctrl* c, int polls, uint64_t* x) {
   long spins = 0;
   while (want) {
 #pragma unroll
@@ -74,7 +73,7 @@ __device__ __forceinline__ bool poll_words(const uint64_t* p, const int* i, uint
     for (int k = 0; k < K; ++k)
       if (((want >> k) & 1) && (uint32_t)(x[k] >> 48) == tag) want &= ~(1u << k);
     if (!want) break;
-    if (++spins > kResSpinLimit)
+    if (++spins > polls)
       __hip_atomic_store(&c->abort.v, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((spins & 1023) == 0 &&
         __hip_atomic_load(&c->abort.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
@@ -204,7 +203,7 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
 #pragma unroll
       for (int k = 0; k < 2; ++k)
         if (w[k] < 2 * lay.chunks && open32(w[k])) want |= 1u << k;
-      if (!poll_words<2>(wins, w, want, q, a.ctrl, x)) bad = 1;
+      if (!poll_words<2>(wins, w, want, q, a.ctrl, r.polls, x)) bad = 1;
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         uint32_t m = (uint32_t)x[k];
@@ -273,7 +272,7 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
         const int ch = i[f] / kChunkWords;
         if (ch < lay.chunks && ch % P != g && open6(ch, i[f] % kChunkWords)) want |= 1u << f;
       }
-      if (!poll_words<kFly>(states, i, want, q, a.ctrl, x)) bad = 1;
+      if (!poll_words<kFly>(states, i, want, q, a.ctrl, r.polls, x)) bad = 1;
 #pragma unroll
       for (int f = 0; f < kFly; ++f) {
         if (!((want >> f) & 1)) continue;

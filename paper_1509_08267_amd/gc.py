@@ -31,7 +31,7 @@ GC_ROWPTR_I64, GC_VALIDATE, GC_ROWS_SORTED = 1, 2, 4
  GC_OPT_CHUNK_ROUNDS, GC_OPT_MEDIUM_DEGREE, GC_OPT_MAX_DEGREE, GC_OPT_MEDIUM_COUNT,
  GC_OPT_HEAVY_COUNT, GC_OPT_PERSISTENT_BLOCKS_PER_CU, GC_OPT_STATE_BYTES,
  GC_OPT_PROFILE, GC_OPT_ALGORITHM, GC_OPT_PARTITIONS, GC_OPT_ORDER,
- GC_OPT_ORDER_SEED) = range(1, 18)
+ GC_OPT_ORDER_SEED, GC_OPT_WAIT_POLLS) = range(1, 19)
 GC_ORDER_NATURAL, GC_ORDER_LARGEST_FIRST, GC_ORDER_RANDOM = range(3)
 ORDERS = {"natural": GC_ORDER_NATURAL, "largest_first": GC_ORDER_LARGEST_FIRST,
           "random": GC_ORDER_RANDOM}
@@ -316,7 +316,7 @@ class Graph:
              "persistent_blocks_per_cu": GC_OPT_PERSISTENT_BLOCKS_PER_CU,
              "profile": GC_OPT_PROFILE, "algorithm": GC_OPT_ALGORITHM,
              "partitions": GC_OPT_PARTITIONS, "order": GC_OPT_ORDER,
-             "order_seed": GC_OPT_ORDER_SEED}
+             "order_seed": GC_OPT_ORDER_SEED, "wait_polls": GC_OPT_WAIT_POLLS}
 
     def set(self, name: str, value):
         if name == "mode" and isinstance(value, str):
