@@ -70,6 +70,13 @@ __device__ __forceinline__ void store_system(int32_t* p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Waits until this wavefront's stores and atomics are complete.  In front of a workgroup barrier
+// after which one thread releases to other workgroups: its release fence writes the L2 back for
+// all, but waits for its own wavefront's operations only.  (The fence in every wavefront would do
+// as well, at the price of as many write-backs: a team's barriers took up to two and a half times
+// as long.)
+__device__ __forceinline__ void drain_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // tentative colour carried by a state word (final colours decode to themselves)
 __device__ __forceinline__ int tent_of(int s) { return s < 0 ? ~s : s; }
 

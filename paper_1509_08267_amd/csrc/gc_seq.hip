@@ -310,7 +310,8 @@ __global__ __launch_bounds__(kBlock) void k_flow_finish(FlowArgs a, int32_t* out
     store_system(&out[kFinishHeader + 1 + 2 * blockIdx.x], left);
     if (round) atomicMax(&a.ctrl->last_round.v, round);
   }
-  __syncthreads();  // every thread's adds are issued
+  drain_stores();  // every thread's adds
+  __syncthreads();
   if (threadIdx.x == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     last = __hip_atomic_fetch_add(&a.ctrl->bar.v, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
