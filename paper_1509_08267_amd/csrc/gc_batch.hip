@@ -921,6 +921,7 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
 // the team's abort flag, after which the team's barriers return at once.
 __device__ __forceinline__ bool team_barrier(TeamCtrl* tc, int K, unsigned& phase) {
   __shared__ int sh_abort;
+  drain_stores();
   __syncthreads();
   if (threadIdx.x == 0) {
     ++phase;

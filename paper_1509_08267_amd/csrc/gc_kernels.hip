@@ -1181,6 +1181,7 @@ __global__ __launch_bounds__(kBlock) void k_finish_fused(KArgs a, AloneArgs w, i
 // barrier returns at once, so the kernel always drains.
 __device__ __forceinline__ bool grid_barrier(Ctrl* c, unsigned& epoch) {
   __shared__ int sh_abort;
+  drain_stores();
   __syncthreads();
   if (threadIdx.x == 0) {
     ++epoch;
