@@ -682,7 +682,7 @@ static int color_blocks_masks(gc_ctx* h, int32_t* colors_out, int32_t* user_out,
     K = 8;
   }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));
-  LCHECK(h, gc::launch_finish(a, 1, h->fin_dev, s));
+  LCHECK(h, gc::launch_finish(a, 1, false, h->fin_dev, s));
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[3], s));
   h->pending_profile = h->profile;
   int rc = permute_back(h, colors_out, user_out, s);
@@ -754,7 +754,7 @@ static int color_blocks(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipSt
   // a round cap can stop the loop with coloured vertices still in conflict
   if (h->n > 0 && h->host->flag) LCHECK(h, gc::launch_blocks_set_left(h->ctrl, h->host->flag, s));
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));
-  LCHECK(h, gc::launch_finish(a, 4, h->fin_dev, s));
+  LCHECK(h, gc::launch_finish(a, 4, false, h->fin_dev, s));
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[3], s));
   h->pending_profile = h->profile;
   rc = permute_back(h, colors_out, user_out, s);
@@ -901,28 +901,13 @@ static bool reserve_resident(gc_ctx* h) {
   return false;
 }
 
-// With R known, the round after which the core pass takes over: the first one
-// that leaves few enough vertices, if enough rounds follow.
-static int decide_core(gc_ctx* h) {
-  h->core_round = -1;
-  const int64_t R = h->known_rounds;
-  if (h->n <= gc::kCoreMax || R <= kCoreMinRounds || R > gc::kTraceRounds || !may_use_core(h))
-    return GC_OK;
-  int32_t* sizes = new (std::nothrow) int32_t[R];
-  if (!sizes) return GC_OK;
-  const hipError_t e = hipMemcpy(sizes, h->ctrl->trace, R * sizeof(int32_t), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) {
-    const int64_t r = std::lower_bound(sizes, sizes + R, (int32_t)gc::kCoreMax,
-                                       [](int32_t x, int32_t most) { return x > most; }) - sizes;
-    if (R - r >= kCoreMinRounds) {  // |U_{r + 1}| = sizes[r]
-      h->core_round = r;
-      h->core_size = sizes[r];
-    }
-  }
-  delete[] sizes;
-  HIPCHECK(h, e);
-  if (h->core_round >= 0 && !reserve_core(h)) h->core_round = -1;  // (later calls allocate nothing)
-  return GC_OK;
+// With R just learned, the round after which the core pass takes over in later calls: the first
+// one that leaves few enough vertices (found by the finishing kernel), if enough rounds follow.
+static void decide_core(gc_ctx* h) {
+  const int64_t R = h->known_rounds, r = h->host->fin[5];
+  const bool core = r >= 1 && R - r >= kCoreMinRounds && R <= gc::kTraceRounds && may_use_core(h);
+  h->core_round = core ? r : -1;
+  h->core_size = core ? h->host->fin[6] : 0;
 }
 
 // The rounds after round0 as one core pass over at most `size` vertices.
@@ -1094,7 +1079,7 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
     } else if (mode == GC_MODE_GRAPH && h->known_rounds > 0) {
       // R is known: queue rounds 2..R, or those before the core pass, in one
       // captured chunk, no read-back.
-      const bool core = h->core_round >= 1 && may_use_core(h);
+      const bool core = h->core_round >= 1 && may_use_core(h) && reserve_core(h);
       const int K = (int)(core ? h->core_round : h->known_rounds) - 1;
       if (K > 0) {
         if (!usable(h->exact, K, L, grid, a)) {
@@ -1136,6 +1121,8 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
         }
         r = upto;
       }
+      // later calls may end in the core pass: its scratch now, while nothing is queued
+      if (r > kCoreMinRounds && h->n > gc::kCoreMax && may_use_core(h)) (void)reserve_core(h);
     }
   }
   if (h->profile) HIPCHECK(h, hipEventRecord(h->pev[2], s));
@@ -1147,7 +1134,7 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   if (h->fused != gc_ctx::kNone && !check)
     LCHECK(h, gc::launch_finish_fused(a, h->sbytes, w, h->fin_dev, s));
   else
-    LCHECK(h, gc::launch_finish(a, h->sbytes, h->fin_dev, s));
+    LCHECK(h, gc::launch_finish(a, h->sbytes, h->known_rounds == 0 && !use_seq(h), h->fin_dev, s));
   if (check) {
     HIPCHECK(h, hipStreamSynchronize(s));
     if (h->host->fin[4] || h->host->fin[1]) {  // again, by the rounds' own passes
@@ -1203,7 +1190,7 @@ static int wait_done(gc_ctx* h) {
   if (h->max_rounds == 0 && h->known_rounds != h->host->last_round) {
     h->known_rounds = h->host->last_round;
     h->known_colors = h->host->ncolors;
-    return decide_core(h);
+    decide_core(h);
   }
   return GC_OK;
 }

@@ -35,7 +35,7 @@ constexpr int kDeferRow = 512;      // a wavefront- or workgroup-class winner wi
                                     // than this left to push queues them for the grid-wide push pass
 constexpr int kPieceEntries = 1024; // row entries of one piece of that pass: one workgroup,
                                     // four entries per thread in flight, one step
-constexpr int kFinishHeader = 5;   // its leading output words (see launch_finish)
+constexpr int kFinishHeader = 7;   // its leading output words (see launch_finish)
 constexpr int kFinishWords = kFinishHeader + 2 * kFinishBlocks;
 
 // One 128-byte line per field that different blocks write, so that flags and
@@ -264,11 +264,13 @@ int launch_report(const KArgs& a, int round, int32_t* out, void* stream);
 // device-visible pinned host memory) receives, by system-scope stores:
 //   out[0] last round, out[1] abort flag, out[2] uncoloured count recorded by
 //   earlier passes (ctrl->left), out[3] workgroups G of this pass, out[4]
-//   whether the core or resident pass could not run, and for each workgroup b < G:
-//   out[5 + 2b] = its largest colour + 1 (0 if none), out[6 + 2b] = its
-//   uncoloured vertices.
+//   whether the core or resident pass could not run, out[5] the round after which
+//   a core pass could take over (the first one that leaves at most kCoreMax
+//   vertices; -1 if there is none, or without `find_core`), out[6] the vertices
+//   it leaves, and for each workgroup b < G: out[7 + 2b] = its largest colour + 1
+//   (0 if none), out[8 + 2b] = its uncoloured vertices.
 // The host folds them once the stream has passed this kernel.
-int launch_finish(const KArgs& a, int sbytes, int32_t* out, void* stream);
+int launch_finish(const KArgs& a, int sbytes, bool find_core, int32_t* out, void* stream);
 
 // After a core or resident pass whose result nobody looks at before it is used:
 // when a wait in it gave up (ctrl->abort), the vertices it had are coloured again

@@ -1040,7 +1040,7 @@ __global__ __launch_bounds__(kBlock) void k_report(KArgs a, int round, int32_t* 
 // per-workgroup pairs.
 // `alone`: the first workgroup takes all vertices.
 template <typename S, bool VEC>
-__device__ __forceinline__ void finish(const KArgs& a, int32_t* out, bool alone) {
+__device__ __forceinline__ void finish(const KArgs& a, int32_t* out, bool alone, int core) {
   __shared__ int sh_max[kWavesPerBlock], sh_left[kWavesPerBlock];
   constexpr int V = 16 / (int)sizeof(S);
   const S* __restrict__ st = (const S*)a.st;
@@ -1097,14 +1097,32 @@ __device__ __forceinline__ void finish(const KArgs& a, int32_t* out, bool alone)
       store_system(&out[2], a.ctrl->left.v);
       store_system(&out[3], (int32_t)gridDim.x);
       store_system(&out[4], alone ? kRecoloured : a.ctrl->core_fail.v);
+      store_system(&out[5], core);
+      store_system(&out[6], core >= 0 ? a.ctrl->trace[core] : 0);
     }
   }
 }
 
+// The round r with |U_r| > kCoreMax >= |U_{r + 1}|, -1 for none (one workgroup).
+__device__ int find_core_round(const Ctrl* ctrl) {
+  __shared__ int sh;
+  if (threadIdx.x == 0) sh = -1;
+  __syncthreads();
+  const int R = min(ctrl->last_round.v, kTraceRounds);
+  for (int r = 1 + (int)threadIdx.x; r < R; r += kBlock)
+    if (ctrl->trace[r - 1] > kCoreMax && ctrl->trace[r] <= kCoreMax) sh = r;
+  __syncthreads();
+  return sh;
+}
+
 template <typename S, bool VEC>
-__global__ __launch_bounds__(kBlock) void k_finish(KArgs a, int32_t* out) {
-  if (blockIdx.x == 0) fold_trace(a.ctrl, a.part);  // the last detect pass's round size
-  finish<S, VEC>(a, out, false);
+__global__ __launch_bounds__(kBlock) void k_finish(KArgs a, int find_core, int32_t* out) {
+  int core = -1;
+  if (blockIdx.x == 0) {
+    fold_trace(a.ctrl, a.part);  // the last detect pass's round size
+    if (find_core) core = find_core_round(a.ctrl);
+  }
+  finish<S, VEC>(a, out, false, core);
 }
 
 // The rounds of w's vertices by one workgroup, a wavefront per vertex: slow, but
@@ -1171,7 +1189,7 @@ __global__ __launch_bounds__(kBlock) void k_finish_fused(KArgs a, AloneArgs w, i
     else color_alone<int32_t, S>(a, w);
     __syncthreads();
   }
-  finish<S, VEC>(a, out, alone);
+  finish<S, VEC>(a, out, alone, -1);
 }
 
 // Grid-wide barrier of a co-resident (cooperative) grid.  Arrivals count up
@@ -1462,8 +1480,8 @@ int launch_report(const KArgs& a, int round, int32_t* out, void* stream) {
   return (int)hipGetLastError();
 }
 
-static int launch_finish_of(const KArgs& a, int sbytes, const AloneArgs* w, int32_t* out,
-                            hipStream_t s) {
+static int launch_finish_of(const KArgs& a, int sbytes, const AloneArgs* w, int find_core,
+                            int32_t* out, hipStream_t s) {
   if (sbytes != 1 && sbytes != 2 && sbytes != 4) return (int)hipErrorInvalidValue;
   // 16 bytes of state per thread, at most kFinishBlocks workgroups
   const long per = (16l / sbytes) * kBlock;
@@ -1471,7 +1489,7 @@ static int launch_finish_of(const KArgs& a, int sbytes, const AloneArgs* w, int3
   const bool vec = ((uintptr_t)a.st % 16 == 0) && ((uintptr_t)a.colors % 16 == 0);
 #define GC_FINISH(S_, VEC_)                                                                   \
   if (w) hipLaunchKernelGGL((k_finish_fused<S_, VEC_>), dim3(grid), dim3(kBlock), 0, s, a, *w, out); \
-  else hipLaunchKernelGGL((k_finish<S_, VEC_>), dim3(grid), dim3(kBlock), 0, s, a, out)
+  else hipLaunchKernelGGL((k_finish<S_, VEC_>), dim3(grid), dim3(kBlock), 0, s, a, find_core, out)
 #define GC_FINISH_VEC(S_)    \
   if (vec) {                 \
     GC_FINISH(S_, true);     \
@@ -1490,13 +1508,13 @@ static int launch_finish_of(const KArgs& a, int sbytes, const AloneArgs* w, int3
   return (int)hipGetLastError();
 }
 
-int launch_finish(const KArgs& a, int sbytes, int32_t* out, void* stream) {
-  return launch_finish_of(a, sbytes, nullptr, out, (hipStream_t)stream);
+int launch_finish(const KArgs& a, int sbytes, bool find_core, int32_t* out, void* stream) {
+  return launch_finish_of(a, sbytes, nullptr, find_core, out, (hipStream_t)stream);
 }
 
 int launch_finish_fused(const KArgs& a, int sbytes, const AloneArgs& w, int32_t* out,
                         void* stream) {
-  return launch_finish_of(a, sbytes, &w, out, (hipStream_t)stream);
+  return launch_finish_of(a, sbytes, &w, 0, out, (hipStream_t)stream);
 }
 
 int launch_classify(const void* rowptr, bool rp64, int32_t n, int32_t light_max, int32_t heavy_min,

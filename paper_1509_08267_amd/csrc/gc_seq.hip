@@ -343,6 +343,8 @@ __global__ __launch_bounds__(kBlock) void k_flow_finish(FlowArgs a, int32_t* out
     store_system(&out[2], 0);
     store_system(&out[3], (int32_t)gridDim.x);
     store_system(&out[4], 0);
+    store_system(&out[5], -1);
+    store_system(&out[6], 0);
   }
 }
 
