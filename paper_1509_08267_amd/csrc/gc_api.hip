@@ -903,9 +903,10 @@ static bool reserve_resident(gc_ctx* h) {
 
 // With R just learned, the round after which the core pass takes over in later calls: the first
 // one that leaves few enough vertices (found by the finishing kernel), if enough rounds follow.
+// The call that learned R need not be one that may use the pass.
 static void decide_core(gc_ctx* h) {
   const int64_t R = h->known_rounds, r = h->host->fin[5];
-  const bool core = r >= 1 && R - r >= kCoreMinRounds && R <= gc::kTraceRounds && may_use_core(h);
+  const bool core = r >= 1 && R - r >= kCoreMinRounds && R <= gc::kTraceRounds;
   h->core_round = core ? r : -1;
   h->core_size = core ? h->host->fin[6] : 0;
 }
