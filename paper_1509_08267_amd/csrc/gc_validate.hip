@@ -52,7 +52,7 @@ __global__ void k_validate(const RP* rowptr, const int32_t* colidx, int32_t n, i
       fail(2, v);
       continue;
     }
-    for (RP k = b + gl; k < e; k += kRowLanes) {
+    for (int64_t k = (int64_t)b + gl; k < e; k += kRowLanes) {
       int u = colidx[k];
       if (u < 0 || u >= n) {
         fail(3, v);
