@@ -1167,13 +1167,8 @@ static int batch_cus() {
 
 static int run_batch(int64_t G, gc_graph_desc* d, const int32_t* rpb, const int32_t* cib,
                      int32_t* colb, int max_rounds, void* ws, hipStream_t s) {
-  static bool lds_set = false;
-  if (!lds_set) {  // allow the dynamic slice on top of the static LDS
-    hipError_t e = hipFuncSetAttribute((const void*)k_batch_color,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kBatchLds);
-    if (e != hipSuccess) return (int)e;
-    lds_set = true;
-  }
+  const int rc = allow_lds((const void*)k_batch_color, kBatchLds);
+  if (rc) return rc;
   BatchCtrl* ctrl = (BatchCtrl*)ws;
   TeamCtrl* teams = (TeamCtrl*)((char*)ws + ws_teams_off());
   int32_t* order = (int32_t*)((char*)ws + ws_order_off());

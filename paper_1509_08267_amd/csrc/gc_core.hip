@@ -328,10 +328,8 @@ template <typename RP, typename S>
 int launch_core_t(const KArgs& a, const CoreArgs& c, int round0, int last, int workgroups,
                   hipStream_t s) {
   static_assert(sizeof(CoreSmem) <= 80 * 1024, "two workgroups per compute unit");
-  hipError_t e = hipFuncSetAttribute((const void*)&k_core<RP, S>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)sizeof(CoreSmem));
-  if (e != hipSuccess) return (int)e;
+  const int rc = allow_lds((const void*)&k_core<RP, S>, (int)sizeof(CoreSmem));
+  if (rc) return rc;
   hipLaunchKernelGGL((k_core<RP, S>), dim3(workgroups), dim3(kCoreBlock), sizeof(CoreSmem), s, a, c,
                      round0, last);
   return (int)hipGetLastError();

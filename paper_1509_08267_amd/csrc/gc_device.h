@@ -21,6 +21,13 @@ __device__ __forceinline__ uint64_t shfl_xor64(uint64_t x, int mask) {
   return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
 }
 
+// Allows kernel f `bytes` of dynamic LDS.  Called before every launch of such a kernel: the
+// attribute belongs to the current device, so that setting it once per process would miss the
+// others (and need an order between threads).
+inline int allow_lds(const void* f, int bytes) {
+  return (int)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
 template <typename T>
 __device__ __forceinline__ T shfl_any(T x, int src);
 template <>

@@ -295,13 +295,8 @@ __global__ __launch_bounds__(kResBlock) void k_resident(KArgs a, ResArgs r, int 
 
 template <typename RP>
 int launch_resident_t(const KArgs& a, const ResArgs& r, int last, int groups, hipStream_t s) {
-  static bool lds_set = false;
-  if (!lds_set) {
-    const hipError_t e = hipFuncSetAttribute((const void*)&k_resident<RP>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kResLds);
-    if (e != hipSuccess) return (int)e;
-    lds_set = true;
-  }
+  const int rc = allow_lds((const void*)&k_resident<RP>, kResLds);
+  if (rc) return rc;
   hipLaunchKernelGGL((k_res_prepare<RP>), dim3(groups), dim3(kWave), 0, s, a, r, kResLds);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return (int)e;
