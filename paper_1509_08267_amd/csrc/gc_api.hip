@@ -122,6 +122,7 @@ struct gc_ctx {
   bool stats_ready = false;
   int64_t known_rounds = 0;  // R of this graph once a call has completed (0 = unknown)
   int32_t known_colors = 0;  // and the colours of that call
+  int call_family = 0;       // what the last call computed (family_of)
   int64_t partitions = 0;    // p of GC_ALGO_BLOCKS (0 = auto)
   int32_t* bslot = nullptr;  // device, nnz: ForbiddenColors slots (GC_ALGO_BLOCKS)
   uint8_t* btodo = nullptr;  // device, n
@@ -981,6 +982,7 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
   (void)hipGetLastError();  // launch checks below must see only this call's errors
   drop_recoloured(h);
   h->fused = gc_ctx::kNone;
+  h->call_family = family_of(h->algorithm);
   if (h->algorithm == GC_ALGO_BLOCKS) {
     const bool masks = h->n > 0 && h->sbytes == 1 &&
                        (h->n + partitions_of(h) - 1) / partitions_of(h) <= gc::kBlkMaxVertices;
@@ -1188,7 +1190,8 @@ static int wait_done(gc_ctx* h) {
     return set_err(h, GC_EINVAL, "%d vertices uncoloured after the known %d rounds: the graph "
                    "changed after gc_create", h->host->left, h->host->last_round);
   }
-  if (h->max_rounds == 0 && h->known_rounds != h->host->last_round) {
+  if (h->max_rounds == 0 && h->call_family == family_of(h->algorithm) &&
+      h->known_rounds != h->host->last_round) {
     h->known_rounds = h->host->last_round;
     h->known_colors = h->host->ncolors;
     decide_core(h);
