@@ -9,12 +9,14 @@
 //     first (work buckets by log2 of the CSR size: longest-processing-time
 //     order, so the big graphs do not finish last);
 //   - a workgroup has a compute unit to itself and keeps the state of a graph
-//     of up to 54,000 vertices (maximum degree up to 127) in LDS together with
-//     a mask of the colours taken at each vertex, which a committing vertex
-//     marks in its neighbours (run_graph_push); the rows are all that is left
-//     to read.  Other graphs gather their neighbours' states every round, from
-//     LDS where the state alone fits there (int8, int16 or int32 by the maximum
-//     degree), else from an int32 state in the caller's colour array;
+//     of up to 81,408 vertices (40,704 above a maximum degree of 127) in LDS
+//     together with a mask of the colours taken at each vertex, which a
+//     committing vertex marks in its neighbours (run_graph_push); the rows are
+//     all that is left to read.  Other graphs gather their neighbours' states
+//     every round, from LDS where the state alone fits there (int8 or int16 by
+//     the maximum degree), else from an int32 state in the caller's colour array;
+//   - a launch of many graphs that are nearly all small takes workgroups of a
+//     quarter of the size, several to a compute unit (k_batch_small);
 //   - the rounds are separated by workgroup barriers instead of grid-wide
 //     ones, and each graph stops independently when its round has no loser;
 //   - a graph that would outlast the rest of the launch (k_batch_plan) and has
@@ -33,6 +35,7 @@
 
 #include <climits>
 #include <cstdint>
+#include <type_traits>
 #include <mutex>
 
 #include "gc.h"
@@ -68,13 +71,21 @@ constexpr int64_t kMinTeamWork = 65536; // work (entries + vertices) per team me
 // at most kMinTeam work is done sooner alone than a team's barriers take.
 constexpr uint64_t kTeamCost = 5;
 constexpr uint64_t kMinTeam = 200000;
+// Graphs that k_batch_small colours when there are many (see there).
+constexpr int kSmallBlock = 256;
+constexpr int kSmallMax = 4096;           // vertices at most
+constexpr int kSmallBuckets = 16;         // work below 2^16
+constexpr int kSmallLds = kSmallMax * 4;
+constexpr int kSmallPerCu = 4;            // workgroups per CU (their registers)
 constexpr int kFine = 512;  // work histogram of the plan: eight buckets per power of two
 constexpr long kTeamSpinLimit = 1l << 25;
 
 struct BatchCtrl {
   int32_t queue;    // next position in `order`
-  int32_t tickets;  // entries of `order`: one per graph, K per team graph
-  int32_t pad[62];
+  int32_t tickets;  // entries of `order` for k_batch_color: one per graph, K per team graph
+  int32_t small_queue;  // the same for k_batch_small, whose entries follow:
+  int32_t small_end;    // [tickets, small_end)
+  int32_t pad[60];
 };
 
 // Control words of one team (one 256-byte line each).
@@ -152,8 +163,9 @@ __device__ __forceinline__ uint64_t batch_work(const gc_graph_desc& x, const int
   return (uint64_t)nnz + (uint64_t)x.n + 1;
 }
 
-// What a graph costs a workgroup of its own: a graph beyond the pushed-colour
-// path's LDS slice gathers, as a team would.
+// What a graph costs a workgroup of its own: a graph beyond the masks of sixteen
+// colours gathers, as a team would, or, up to 81,408 vertices, at least where its
+// eight run out.
 __device__ __forceinline__ uint64_t cost_alone(int n, uint64_t w) {
   return n > (kBatchLds - 4) / 3 ? kTeamCost * w : w;
 }
@@ -168,29 +180,45 @@ __device__ __forceinline__ uint64_t fine_end(int b) {
   return ((uint64_t)(9 + (b & 7)) << (b >> 3)) >> 3;
 }
 
+__device__ __forceinline__ bool is_small(int n, uint64_t w) {
+  return n <= kSmallMax && w < (1ull << kSmallBuckets);
+}
+// Bucket of the order: below kSmallBuckets the graphs of k_batch_small, behind all others.
+__device__ __forceinline__ int order_bucket(bool small, uint64_t w) {
+  const int p = 63 - __builtin_clzll(w);
+  return small ? p : min(kSmallBuckets + p, kBuckets - 1);
+}
+
 __global__ __launch_bounds__(1024) void k_batch_plan(int64_t G, const gc_graph_desc* d,
                                                      const int32_t* rowptr_base, int32_t* order,
                                                      int32_t* slot, int32_t* gk, TeamCtrl* teams,
-                                                     BatchCtrl* ctrl, int nwg) {
+                                                     BatchCtrl* ctrl, int nwg, int small) {
   __shared__ int hist[kBuckets];
   __shared__ int base[kBuckets];
   __shared__ unsigned long long alone[kFine], work[kFine];  // by cost alone
+  __shared__ unsigned long long large;  // work of the graphs that are not small
   __shared__ int nteams, extra, len;
   for (int i = threadIdx.x; i < kBuckets; i += blockDim.x) hist[i] = 0;
   for (int i = threadIdx.x; i < kFine; i += blockDim.x) alone[i] = work[i] = 0;
   if (threadIdx.x == 0) {
     nteams = 0;
     extra = 0;
+    large = 0;
     len = kFine - 1;
   }
   __syncthreads();
+  uint64_t mine = 0;
   for (long g = threadIdx.x; g < G; g += blockDim.x) {
     const uint64_t w = batch_work(d[g], rowptr_base);
     const uint64_t c = cost_alone(d[g].n, w);
     const int b = fine_bucket(c);
     atomicAdd(&alone[b], (unsigned long long)c);
     atomicAdd(&work[b], (unsigned long long)w);
+    mine += is_small(d[g].n, w) ? 0 : w;
   }
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) mine += shfl_xor64(mine, off);
+  if (lane_id() == 0 && mine) atomicAdd(&large, (unsigned long long)mine);
   __syncthreads();
   // prefix sums of `alone`, suffix sums of `work` (buckets above), in place
   const int b = threadIdx.x;
@@ -213,6 +241,8 @@ __global__ __launch_bounds__(1024) void k_batch_plan(int64_t G, const gc_graph_d
   }
   __syncthreads();
   const uint64_t T = fine_end(len);
+  // k_batch_small runs after k_batch_color: only where that has next to nothing to do
+  if (small) small = large <= work[0] / 64;
   for (long g = threadIdx.x; g < G; g += blockDim.x) {
     const uint64_t w = batch_work(d[g], rowptr_base);
     uint64_t q = 0;
@@ -241,7 +271,7 @@ __global__ __launch_bounds__(1024) void k_batch_plan(int64_t G, const gc_graph_d
       }
     }
     gk[g] = k | ((s + 1) << 16);
-    atomicAdd(&hist[63 - __builtin_clzll(w)], k);
+    atomicAdd(&hist[order_bucket(small && is_small(d[g].n, w), w)], k);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -249,15 +279,16 @@ __global__ __launch_bounds__(1024) void k_batch_plan(int64_t G, const gc_graph_d
     for (int b = kBuckets - 1; b >= 0; --b) {
       base[b] = acc;
       acc += hist[b];
+      if (b == kSmallBuckets) ctrl->tickets = acc;
     }
-    ctrl->queue = 0;
-    ctrl->tickets = acc;
+    ctrl->queue = ctrl->small_queue = 0;
+    ctrl->small_end = acc;
   }
   __syncthreads();
   for (long g = threadIdx.x; g < G; g += blockDim.x) {
     const uint64_t w = batch_work(d[g], rowptr_base);
     const int k = gk[g] & 0xffff, s = (gk[g] >> 16) - 1;
-    const int pos = atomicAdd(&base[63 - __builtin_clzll(w)], k);
+    const int pos = atomicAdd(&base[order_bucket(small && is_small(d[g].n, w), w)], k);
     for (int j = 0; j < k; ++j) {
       order[pos + j] = (int32_t)g;
       slot[pos + j] = s;
@@ -396,20 +427,24 @@ __device__ __forceinline__ bool detect_quads(const int32_t* __restrict__ ci,
   return false;
 }
 
+// Lanes per item when cnt (>= 1) items share a wavefront: the largest power of
+// two that gives every item a group at once.
+__device__ __forceinline__ int group_lanes(int cnt) {
+  return kWave >> (cnt <= 1 ? 0 : 32 - __builtin_clz((unsigned)cnt - 1));
+}
+
 // One pass (speculate or detect) of one round over the graph's uncoloured
 // vertices by the whole workgroup (member `rank` of a team of K; 0 of 1
 // alone): each wavefront walks 64-vertex chunks, ballots the uncoloured ones
-// and hands them to its groups of L lanes.  `skipv` (or null) holds each
+// and hands them to its groups of L0 lanes, or of more when it has few of them
+// (those left late are the ones with long rows: 600 R-MAT graphs of scale 17 that
+// gather alone 1,372 -> 558 ms, 64 of scale 16 in teams 136 -> 46).  `skipv` (or null) holds each
 // vertex's resume offset for the detect scans; `mirror` (or null) receives
 // every state write as well (a team's shared copy).
 template <typename S, bool SPEC>
-__device__ __forceinline__ bool graph_pass(const GraphRun& g, S* st, int32_t* skipv, int L,
+__device__ __forceinline__ bool graph_pass(const GraphRun& g, S* st, int32_t* skipv, int L0,
                                            int rank = 0, int K = 1, int32_t* mirror = nullptr) {
   const int lane = lane_id();
-  const int gl = lane & (L - 1);
-  const int grp = lane / L;
-  const int Gw = kWave / L;
-  const uint64_t gmask = (L == kWave) ? ~0ull : (((1ull << L) - 1) << (grp * L));
   const int wave = threadIdx.x / kWave;
   const auto state = [st](int u) { return (int)st[u]; };
   bool lost = false;
@@ -428,7 +463,11 @@ __device__ __forceinline__ bool graph_pass(const GraphRun& g, S* st, int32_t* sk
     const uint64_t am = __ballot(act);
     if (am == 0) continue;
     const int cnt = __popcll(am);
-    for (int p = 0; p < cnt; p += Gw) {
+    const int L = max(L0, group_lanes(cnt));
+    const int gl = lane & (L - 1);
+    const int grp = lane / L;
+    const uint64_t gmask = (L == kWave) ? ~0ull : (((1ull << L) - 1) << (grp * L));
+    for (int p = 0; p < cnt; p += kWave / L) {
       const int k = p + grp;
       const bool valid = k < cnt;
       const int pos = nth_set_bit(am, valid ? k : 0);
@@ -525,54 +564,60 @@ __device__ __forceinline__ int run_graph(const GraphRun& g, S* st, int L, int* l
 }
 
 // A graph's colouring state in the LDS slice under pushed colours: per
-// vertex its state (8 bits: ~t or the final colour, so the maximum degree is
-// at most 127) and a mask of the colours below BITS that are final on a
-// neighbour.  BITS = 24 packs both into one word (4 bytes per vertex); 16
-// takes 3 bytes, two masks to a word behind the states.
-template <int BITS>
+// vertex its state (~t or the final colour, in STATE bits: 8 up to a maximum
+// degree of 127, 16 up to 32,767) and a mask of the colours below BITS that are
+// final on a neighbour.  <24, 8> packs both into a word of 4 bytes, <16, 16> as
+// well, <48, 16> into one of 8; <16, 8> takes 3 bytes and <8, 8> 2, two or four
+// masks to a word before the states.
+template <int BITS, int STATE>
 struct Slots {
-  uint32_t* w;
-  int8_t* st;
+  using M = typename std::conditional<(BITS > 32), unsigned long long, uint32_t>::type;
+  using S = typename std::conditional<STATE == 8, int8_t, int16_t>::type;
+  static constexpr int kBits = BITS;
+  static constexpr M kAll = ((M)1 << BITS) - 1;
+  static constexpr bool kPacked = BITS + STATE == 8 * (int)sizeof(M);
+  static constexpr int kStride = kPacked ? (int)(sizeof(M) / sizeof(S)) : 1;
+  static constexpr int kPer = kPacked ? 1 : 32 / BITS;  // masks to a word
+  M* w;
+  S* st;
   __device__ static Slots at(char* smem, int n) {
     Slots x;
-    x.w = (uint32_t*)smem;
-    x.st = BITS == 24 ? (int8_t*)smem + 3 : (int8_t*)(x.w + (n + 1) / 2);
+    x.w = (M*)smem;
+    x.st = kPacked ? (S*)smem + kStride - 1 : (S*)(x.w + words(n));
     return x;
   }
+  __device__ static constexpr int words(int n) { return (n + kPer - 1) / kPer; }
   __device__ static constexpr bool fits(int n) {
-    return BITS == 24 ? n <= kBatchLds / 4 : n <= (kBatchLds - 4) / 3;
+    return n <= kBatchLds && words(n) * (int)sizeof(M) + (kPacked ? 0 : n) <= kBatchLds;
   }
-  __device__ __forceinline__ int state(int v) const { return st[BITS == 24 ? 4 * v : v]; }
-  __device__ __forceinline__ void set_state(int v, int s) const {
-    st[BITS == 24 ? 4 * v : v] = (int8_t)s;
+  __device__ static __forceinline__ int shift(int v) {
+    return kPacked ? 0 : BITS * (int)((unsigned)v % kPer);
   }
-  __device__ __forceinline__ uint32_t mask(int v) const {
-    return BITS == 24 ? w[v] & 0xffffffu : (w[v >> 1] >> (16 * (v & 1))) & 0xffffu;
+  // state s and no mask (the split layout's masks are cleared apart)
+  __device__ __forceinline__ void init(int v, int s) const {
+    if (kPacked) w[v] = (M)(long long)s << (BITS & 63);
+    else set_state(v, s);
+  }
+  __device__ __forceinline__ int state(int v) const { return st[kStride * v]; }
+  __device__ __forceinline__ void set_state(int v, int s) const { st[kStride * v] = (S)s; }
+  __device__ __forceinline__ M mask(int v) const {
+    return (w[(unsigned)v / kPer] >> shift(v)) & kAll;
   }
   // several lanes may mark the vertices of one word
-  __device__ __forceinline__ void mark(int v, uint32_t bits) const {
-    if (BITS == 24) atomicOr(&w[v], bits);
-    else atomicOr(&w[v >> 1], bits << (16 * (v & 1)));
+  __device__ __forceinline__ void mark(int v, M bits) const {
+    atomicOr(&w[(unsigned)v / kPer], bits << shift(v));
   }
 };
-template <int BITS>
-constexpr uint32_t kAllTaken = (1u << BITS) - 1;
-
-// Lanes per item when cnt (>= 1) items share a wavefront: the largest power of
-// two that gives every item a group at once.
-__device__ __forceinline__ int group_lanes(int cnt) {
-  return kWave >> (cnt <= 1 ? 0 : 32 - __builtin_clz((unsigned)cnt - 1));
-}
 
 // A wavefront's vertices that have committed and not yet pushed: row segment
 // [b, e) and colour t in lanes 0 .. cnt - 1.  They push together, a group of
 // lanes each, so that few winners at a time still fill the wavefront.
-template <int BITS>
+template <typename SL>
 struct Winners {
   int b = 0, e = 0, t = 0, cnt = 0;
 
   // marks the queued colours; four quads in flight per lane
-  __device__ __forceinline__ void flush(const Slots<BITS>& sl, const int32_t* __restrict__ ci) {
+  __device__ __forceinline__ void flush(const SL& sl, const int32_t* __restrict__ ci) {
     if (cnt == 0) return;
     const int lane = lane_id();
     const int L = min(16, group_lanes(cnt));
@@ -582,7 +627,7 @@ struct Winners {
       const int vb = __shfl(b, k & (kWave - 1)), ve = __shfl(e, k & (kWave - 1)),
                 vt = __shfl(t, k & (kWave - 1));
       if (k >= cnt) continue;
-      const uint32_t bit = 1u << vt;
+      const typename SL::M bit = (typename SL::M)1 << vt;
       const Quads r = quads_of(ci, vb, ve);
       const int nq = (r.len + 3) >> 2;
       for (int i = gl; i < nq; i += 4 * L) {
@@ -606,9 +651,9 @@ struct Winners {
     cnt = 0;
   }
 
-  // the lanes of wm join the queue (all lanes active; colours below BITS)
-  __device__ __forceinline__ void add(const Slots<BITS>& sl, const int32_t* __restrict__ ci,
-                                      uint64_t wm, int pb, int pe, int pt) {
+  // the lanes of wm join the queue (all lanes active; colours with a mask bit)
+  __device__ __forceinline__ void add(const SL& sl, const int32_t* __restrict__ ci, uint64_t wm,
+                                      int pb, int pe, int pt) {
     const int c = __popcll(wm);
     if (c == 0) return;
     if (cnt + c > kWave) flush(sl, ci);
@@ -636,10 +681,12 @@ constexpr int kPushBatch = 16;  // queued winners that are pushed at once
 // launch: gathering every round 16.8; pushed masks with a chunk's scans and
 // pushes in lockstep 10.9; uncoloured vertices packed across chunks 8.2; a new
 // vertex for every lane that is done, winners pushing sixteen at a time 7.5.
-template <int BITS>
+template <typename SL, int WAVES = kBatchWaves>
 __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int L, int* left) {
+  using M = typename SL::M;
+  constexpr int BITS = SL::kBits;
   __shared__ int sh_cnt;
-  const Slots<BITS> sl = Slots<BITS>::at(smem, g.n);
+  const SL sl = SL::at(smem, g.n);
   const auto state = [sl](int u) { return sl.state(u); };
   int32_t* const skipv = g.out;  // the resume offsets, until the colours are written
   const int lane = lane_id();
@@ -648,12 +695,11 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
   const int nchunks = (g.n + kWave - 1) / kWave;
   bool any = false;
   int r = g.rounds_in;
-  if (BITS == 16)
-    for (int i = threadIdx.x; i < (g.n + 1) / 2; i += blockDim.x) sl.w[i] = 0;
+  if (!SL::kPacked)
+    for (int i = threadIdx.x; i < SL::words(g.n); i += blockDim.x) sl.w[i] = 0;
   for (int v = threadIdx.x; v < g.n; v += blockDim.x) {
     const int s = r == 0 ? -1 : g.out[v];
-    if (BITS == 24) sl.w[v] = (uint32_t)s << 24;
-    else sl.set_state(v, s);
+    sl.init(v, s);
     any |= s < 0;
   }
   __syncthreads();
@@ -661,8 +707,8 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
     // round 1 in closed form (sorted rows): v keeps colour 0 iff no neighbour
     // has a lower id
     any = false;
-    Winners<BITS> wq;
-    for (int ch = wave; ch < nchunks; ch += kBatchWaves) {
+    Winners<SL> wq;
+    for (int ch = wave; ch < nchunks; ch += WAVES) {
       const int v = ch * kWave + lane;
       int b = 0, e = 0;
       bool win = false;
@@ -681,7 +727,7 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
     r = g.n > 0 ? 1 : 0;
   } else {
     // resumed: the masks of the uncoloured vertices from their rows
-    for (int ch = wave; ch < nchunks; ch += kBatchWaves) {
+    for (int ch = wave; ch < nchunks; ch += WAVES) {
       const int v = ch * kWave + lane;
       int b = 0, e = 0;
       bool act = false;
@@ -699,7 +745,7 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
         const int k = p + grp;
         const int pos = nth_set_bit(am, k < cnt ? k : 0);
         const int vb = __shfl(b, pos), ve = __shfl(e, pos);
-        uint32_t m = 0;
+        M m = 0;
         if (k < cnt) {
           const Quads q = quads_of(g.ci, vb, ve);
           for (int i = gl; 4 * i < q.len; i += L) {
@@ -709,11 +755,11 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
             for (int j = 0; j < 4; ++j)
               if (4 * i + j >= q.lead && 4 * i + j < q.len) {
                 const int c = sl.state(u[j]);
-                if (c >= 0 && c < BITS) m |= 1u << c;
+                if (c >= 0 && c < BITS) m |= (M)1 << c;
               }
           }
         }
-        for (int off = L / 2; off > 0; off >>= 1) m |= (uint32_t)__shfl_xor((int)m, off);
+        for (int off = L / 2; off > 0; off >>= 1) m |= __shfl_xor(m, off);
         if (k < cnt && gl == 0 && m) sl.mark(ch * kWave + pos, m);
       }
     }
@@ -724,13 +770,13 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
   // graph then reports uncoloured vertices)
   while (more && r < g.n && (g.max_rounds <= 0 || r - g.rounds_in < g.max_rounds)) {
     ++r;
-    for (int ch = wave; ch < nchunks; ch += kBatchWaves) {  // speculate
+    for (int ch = wave; ch < nchunks; ch += WAVES) {  // speculate
       const int v = ch * kWave + lane;
       bool full = false;
       if (v < g.n && sl.state(v) < 0) {
-        const uint32_t m = sl.mask(v);
-        full = m == kAllTaken<BITS>;
-        if (!full) sl.set_state(v, ~__builtin_ctz(~m));
+        const M m = sl.mask(v);
+        full = m == SL::kAll;
+        if (!full) sl.set_state(v, ~__builtin_ctzll(~(unsigned long long)m));
       }
       const uint64_t fm = __ballot(full);
       if (fm == 0) continue;
@@ -740,13 +786,14 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
         e = g.rp[v + 1];
       }
       const int cnt = __popcll(fm);
-      for (int p = 0; p < cnt; p += Gw) {
-        const int k = p + grp;
+      const int FL = max(L, group_lanes(cnt));  // few such rows are long ones
+      for (int p = 0; p < cnt; p += kWave / FL) {
+        const int k = p + lane / FL;
         const int pos = nth_set_bit(fm, k < cnt ? k : 0);
         const int vb = __shfl(b, pos), ve = __shfl(e, pos);
         if (k < cnt) {
-          const int t = spec_quads(g.ci, state, vb, ve, L, gl, BITS);
-          if (gl == 0) sl.set_state(ch * kWave + pos, ~t);
+          const int t = spec_quads(g.ci, state, vb, ve, FL, lane & (FL - 1), BITS);
+          if ((lane & (FL - 1)) == 0) sl.set_state(ch * kWave + pos, ~t);
         }
       }
     }
@@ -758,12 +805,12 @@ __device__ __forceinline__ int run_graph_push(const GraphRun& g, char* smem, int
     // step has 64 rows to read and a long scan holds up no other; the winners
     // push sixteen at a time while the next step's quads are on their way.
     bool lost = false;
-    Winners<BITS> wq;
+    Winners<SL> wq;
     int ch = wave, pv = 0, pc = 0;  // next chunk; vertices packed so far, in lanes 0 .. pc - 1
     auto next_batch = [&](int& v) {
       while (ch < nchunks) {  // wave-uniform
         const int c0 = ch * kWave;
-        ch += kBatchWaves;
+        ch += WAVES;
         const uint64_t am = __ballot(c0 + lane < g.n && sl.state(min(c0 + lane, g.n - 1)) < 0);
         const int total = pc + __popcll(am);
         if (total == pc) continue;
@@ -1073,15 +1120,43 @@ __device__ __forceinline__ int run_team(const GraphRun& g, char* smem, TeamCtrl*
   return team_rounds<int32_t, false>(g, nullptr, tc, rank, K, L, phase, r, ok, left);
 }
 
+// The widest masks that fit the slice beside the state (8 bits up to a maximum degree of 127, 16 up
+// to 32,767); a state without masks where none do, and the caller's array where that does not fit.
+// With a workgroup to a compute unit a graph that gathers alone has half the wavefronts it had with
+// two, so the masks reach as far as they can.  ms per launch, gathering by two workgroups per unit /
+// by one / with masks: 512 R-MAT graphs of scale 12 and edge factor 8 4.39 / 7.79 / 0.72, of scale
+// 14 61.3 / 66.5 / 2.9, 64 of scale 15 and edge factor 16 46.3 / 123 / 30, 512 graphs of 2,000
+// vertices and average degree 300 11.2 / 15.5 / 4.7, 600 of 60,000 and 16 9.38 / 11.3 / 4.5.
 __device__ __forceinline__ int dispatch_state(const GraphRun& g, int maxdeg, char* smem, int L,
                                               int* left) {
-  if (maxdeg <= 127 && Slots<24>::fits(g.n)) return run_graph_push<24>(g, smem, L, left);
-  if (maxdeg <= 127 && Slots<16>::fits(g.n)) return run_graph_push<16>(g, smem, L, left);
+  if (maxdeg <= 127 && Slots<24, 8>::fits(g.n))
+    return run_graph_push<Slots<24, 8>>(g, smem, L, left);
+  if (maxdeg <= 127 && Slots<16, 8>::fits(g.n))
+    return run_graph_push<Slots<16, 8>>(g, smem, L, left);
+  if (maxdeg <= 127 && Slots<8, 8>::fits(g.n)) return run_graph_push<Slots<8, 8>>(g, smem, L, left);
+  if (maxdeg <= 32767 && Slots<48, 16>::fits(g.n))
+    return run_graph_push<Slots<48, 16>>(g, smem, L, left);
+  if (maxdeg <= 32767 && Slots<16, 16>::fits(g.n))
+    return run_graph_push<Slots<16, 16>>(g, smem, L, left);
   if (maxdeg <= 127 && g.n <= kBatchLds) return run_graph<int8_t, true>(g, (int8_t*)smem, L, left);
   if (maxdeg <= 32767 && 2 * g.n <= kBatchLds)
     return run_graph<int16_t, true>(g, (int16_t*)smem, L, left);
-  if (4 * g.n <= kBatchLds) return run_graph<int32_t, true>(g, (int32_t*)smem, L, left);
   return run_graph<int32_t, false>(g, g.out, L, left);
+}
+
+// The maximum degree of a graph (workgroup-wide; *sh starts at 0) and the lanes per row.
+__device__ __forceinline__ int graph_degrees(const GraphRun& g, int* sh, int* lanes) {
+  int mx = 0;
+  for (int v = threadIdx.x; v < g.n; v += blockDim.x) mx = max(mx, g.rp[v + 1] - g.rp[v]);
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
+  if (lane_id() == 0 && mx) atomicMax(sh, mx);
+  __syncthreads();
+  const double avg = g.n > 0 ? (double)g.rp[g.n] / g.n : 0.0;
+  int L = kMinLanes;
+  while (L < 16 && 2.0 * L * kEntriesPerLane <= avg) L *= 2;
+  *lanes = L;
+  return *sh;
 }
 
 __global__ __launch_bounds__(kBatchBlock, 4) void k_batch_color(gc_graph_desc* d,
@@ -1130,19 +1205,54 @@ __global__ __launch_bounds__(kBatchBlock, 4) void k_batch_color(gc_graph_desc* d
       __syncthreads();  // sh_idx / sh_rank are rewritten for the next entry
       continue;
     }
-    int mx = 0;
-    for (int v = threadIdx.x; v < g.n; v += blockDim.x) mx = max(mx, g.rp[v + 1] - g.rp[v]);
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
-    if (lane_id() == 0 && mx) atomicMax(&sh_max, mx);
+    int left = 0, L = 0;
+    const int maxdeg = graph_degrees(g, &sh_max, &L);
+    const int rounds = dispatch_state(g, maxdeg, smem, L, &left);
+    if (threadIdx.x == 0) {
+      d[gi].rounds = rounds;
+      d[gi].active = left;
+      d[gi].max_degree = maxdeg;
+    }
+    __syncthreads();  // sh_idx / sh_max are rewritten for the next graph
+  }
+}
+
+// Many small graphs (a launch of at least kSmallPerCu graphs per compute unit, nearly all of its
+// work in graphs of up to kSmallMax vertices): workgroups of four wavefronts, several to a
+// compute unit.  A small graph keeps few wavefronts busy and is bound by the chain of loads and
+// barriers of its rounds, so what counts is how many are in flight, where a large one wants the
+// LDS of a compute unit to itself.  20,000 graphs of 100 vertices: 1.73 ms by one workgroup per
+// unit, 1.35 by two of half the LDS, now 0.61; 4,096 of 500: 0.52, 0.46, 0.25.  Beside large graphs
+// the two kernels, one after the other, lose: 1,500 graphs of 100 to 50,000 vertices 1.43 ms
+// against 1.28, 3,000 of 1,000 and two of 300,000 1.22 against 1.15.
+__global__ __launch_bounds__(kSmallBlock, kSmallPerCu) void k_batch_small(
+    gc_graph_desc* d, const int32_t* rowptr_base, const int32_t* colidx_base, int32_t* colors_base,
+    int max_rounds, const int32_t* order, BatchCtrl* ctrl) {
+  extern __shared__ char smem[];
+  __shared__ int sh_idx, sh_max;
+  constexpr int kWaves = kSmallBlock / kWave;
+  const int first = ctrl->tickets, end = ctrl->small_end;
+  for (;;) {
+    if (threadIdx.x == 0) {
+      sh_idx = first + atomicAdd(&ctrl->small_queue, 1);
+      sh_max = 0;
+    }
     __syncthreads();
-    const int maxdeg = sh_max;
-    const int64_t nnz = g.n > 0 ? (int64_t)g.rp[g.n] : 0;
-    const double avg = g.n > 0 ? (double)nnz / g.n : 0.0;
-    int left = 0, rounds;
-    int L = kMinLanes;
-    while (L < 16 && 2.0 * L * kEntriesPerLane <= avg) L *= 2;
-    rounds = dispatch_state(g, maxdeg, smem, L, &left);
+    const int idx = sh_idx;
+    if (idx >= end) break;  // workgroup-uniform
+    const int gi = order[idx];
+    const gc_graph_desc x = d[gi];
+    GraphRun g;
+    g.rp = rowptr_base + x.rowptr_off;
+    g.ci = colidx_base + x.colidx_off;
+    g.out = colors_base + x.color_off;
+    g.n = x.n;
+    g.rounds_in = x.rounds;
+    g.max_rounds = max_rounds;
+    int left = 0, L = 0;
+    const int maxdeg = graph_degrees(g, &sh_max, &L);
+    const int rounds = maxdeg <= 127 ? run_graph_push<Slots<24, 8>, kWaves>(g, smem, L, &left)
+                                     : run_graph_push<Slots<16, 16>, kWaves>(g, smem, L, &left);
     if (threadIdx.x == 0) {
       d[gi].rounds = rounds;
       d[gi].active = left;
@@ -1177,12 +1287,17 @@ static int run_batch(int64_t G, gc_graph_desc* d, const int32_t* rpb, const int3
   // one workgroup per compute unit, all resident at once, whatever the number
   // of graphs: a team can use workgroups beyond one per graph
   const int grid = batch_cus();
+  const bool small = G >= (int64_t)kSmallPerCu * grid;
   hipLaunchKernelGGL(k_batch_plan, dim3(1), dim3(1024), 0, s, G, d, rpb, order, slot, gk, teams,
-                     ctrl, grid);
+                     ctrl, grid, (int)small);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return (int)e;
   hipLaunchKernelGGL(k_batch_color, dim3(grid), dim3(kBatchBlock), kBatchLds, s, d, rpb, cib, colb,
                      max_rounds, order, slot, teams, ctrl);
+  e = hipGetLastError();
+  if (e != hipSuccess || !small) return (int)e;
+  hipLaunchKernelGGL(k_batch_small, dim3(kSmallPerCu * grid), dim3(kSmallBlock), kSmallLds, s, d,
+                     rpb, cib, colb, max_rounds, order, ctrl);
   return (int)hipGetLastError();
 }
 
