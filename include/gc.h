@@ -97,8 +97,9 @@ enum gc_flags {
  * GC_OPT_MEDIUM_DEGREE, and, on sorted rows with such vertices, 4 bytes per
  * CSR entry and per vertex for their lower-neighbour lists; 35 KB for the
  * pass that runs a small graph, or the last rounds of a large one, in one
- * launch) and a small pinned host block; it synchronises
- * `stream` before returning.  The handle belongs to the device current at
+ * launch; with int32 row pointers and more than 2^31 - 8193 entries, 8 bytes
+ * per vertex for a 64-bit copy of them) and a small pinned host block; it
+ * synchronises `stream` before returning.  The handle belongs to the device current at
  * this call.
  * Returns GC_OK, GC_EINVAL, GC_ENOMEM, GC_ETOOBIG or GC_EDEVICE.
  */

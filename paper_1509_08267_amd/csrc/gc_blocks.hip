@@ -219,20 +219,19 @@ __device__ __forceinline__ void chunk_rows(const int32_t* __restrict__ colidx, u
     const int k = p + lane / kBlkLanes;
     const bool valid = k < cnt;
     const int pos = __shfl(from, k & (kWave - 1));
-    const RP vb = shfl_any<RP>(b, pos), ve = shfl_any<RP>(e, pos);
-    const int32_t* at = colidx + vb + gl;
-    int left = valid ? (int)(ve - vb) - gl : 0;  // entries from `at` on
-    while (__ballot(left > 0)) {
+    RP i = shfl_any<RP>(b, pos) + gl;
+    RP ve = shfl_any<RP>(e, pos);
+    if (!valid) ve = i;
+    while (__ballot(i < ve)) {
       int u[4];
       bool ok[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        ok[j] = left > j * kBlkLanes;
-        u[j] = ok[j] ? at[j * kBlkLanes] : 0;
+        ok[j] = i + j * kBlkLanes < ve;
+        u[j] = ok[j] ? colidx[i + j * kBlkLanes] : 0;
       }
       f(pos, valid, u, ok);
-      at += 4 * kBlkLanes;
-      left -= 4 * kBlkLanes;
+      i += 4 * kBlkLanes;
     }
     done(pos, valid);
   }
@@ -482,7 +481,7 @@ int launch_blocks_set_left(Ctrl* c, int value, void* stream) {
 int launch_blocks_init(const BArgs& a, bool rp64, int grid, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   if (rp64) hipLaunchKernelGGL((k_blk_init<int64_t>), dim3(grid), dim3(kBlock), 0, s, a);
-  else hipLaunchKernelGGL((k_blk_init<uint32_t>), dim3(grid), dim3(kBlock), 0, s, a);
+  else hipLaunchKernelGGL((k_blk_init<int32_t>), dim3(grid), dim3(kBlock), 0, s, a);
   return (int)hipGetLastError();
 }
 
@@ -495,7 +494,7 @@ int launch_blocks_init(const BArgs& a, bool rp64, int grid, void* stream) {
 
 int launch_blkm_init(const BArgs& a, bool rp64, int grid, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-#define GC_RP32 uint32_t,
+#define GC_RP32 int32_t,
 #define GC_RP64 int64_t,
   if (rp64) {
     GC_WORDS(k_blkm_init, GC_RP64)
@@ -512,14 +511,14 @@ int launch_blkm_phase(const BArgs& a, bool rp64, int phase, int grid, void* stre
   } else if (rp64) {
     hipLaunchKernelGGL((k_blkm_phase2<int64_t>), dim3(grid), dim3(kBlock), 0, s, a);
   } else {
-    hipLaunchKernelGGL((k_blkm_phase2<uint32_t>), dim3(grid), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL((k_blkm_phase2<int32_t>), dim3(grid), dim3(kBlock), 0, s, a);
   }
   return (int)hipGetLastError();
 }
 
 int launch_blocks_phase(const BArgs& a, bool rp64, int phase, int grid, void* stream) {
   return rp64 ? launch_blocks_phase_t<int64_t>(a, phase, grid, (hipStream_t)stream)
-              : launch_blocks_phase_t<uint32_t>(a, phase, grid, (hipStream_t)stream);
+              : launch_blocks_phase_t<int32_t>(a, phase, grid, (hipStream_t)stream);
 }
 
 }  // namespace gc

@@ -361,7 +361,7 @@ int launch_core(const KArgs& a, bool rp64, int sbytes, const CoreArgs& c, int ro
   if (workgroups < 1 || workgroups > kCoreWords) return (int)hipErrorInvalidValue;
 #define GC_CORE(S_)                                                                 \
   return rp64 ? launch_core_t<int64_t, S_>(a, c, round0, last, workgroups, s)             \
-              : launch_core_t<uint32_t, S_>(a, c, round0, last, workgroups, s)
+              : launch_core_t<int32_t, S_>(a, c, round0, last, workgroups, s)
   if (sbytes == 1) GC_CORE(int8_t);
   if (sbytes == 2) GC_CORE(int16_t);
   GC_CORE(int32_t);

@@ -35,10 +35,6 @@ __device__ __forceinline__ int32_t shfl_any<int32_t>(int32_t x, int src) {
   return __shfl(x, src);
 }
 template <>
-__device__ __forceinline__ uint32_t shfl_any<uint32_t>(uint32_t x, int src) {
-  return (uint32_t)__shfl((int)x, src);
-}
-template <>
 __device__ __forceinline__ int64_t shfl_any<int64_t>(int64_t x, int src) {
   int lo = __shfl((int)(uint32_t)x, src);
   int hi = __shfl((int)(uint32_t)((uint64_t)x >> 32), src);

@@ -167,6 +167,9 @@ bool resident_fits(int64_t n, int64_t m, int sbytes);
 // nothing else done when a workgroup's rows don't fit.
 int launch_resident(const KArgs& a, bool rp64, const ResArgs& r, int last, void* stream);
 
+// 32-bit row pointers as 64-bit ones.
+int launch_widen_rowptr(const int32_t* rowptr, int64_t n, int64_t* out, void* stream);
+
 // Every vertex uncoloured with tentative colour 0 (what precedes round 1).
 int launch_fill_tent0(const KArgs& a, int sbytes, int grid, void* stream);
 

@@ -1186,7 +1186,7 @@ __global__ __launch_bounds__(kBlock) void k_finish_fused(KArgs a, AloneArgs w, i
   const bool alone = a.ctrl->abort.v != 0;
   if (alone && blockIdx.x == 0) {
     if (w.rp64) color_alone<int64_t, S>(a, w);
-    else color_alone<uint32_t, S>(a, w);
+    else color_alone<int32_t, S>(a, w);
     __syncthreads();
   }
   finish<S, VEC>(a, out, alone, -1);
@@ -1411,10 +1411,7 @@ static int persistent_grid_t(int* grid_out) {
   return 0;
 }
 
-// Dispatch on (rowptr width, state width, lanes) to the template instances.  A
-// kernel that walks rows takes 32-bit row pointers (0 .. 2^31 - 1) as unsigned: the
-// position after the last step of a row that ends near 2^31 entries is then still
-// behind the row's end.
+// Dispatch on (rowptr width, state width, lanes) to the template instances.
 #define GC_DISPATCH_L(RP, S, FN, ...)                \
   switch (lanes) {                                   \
     case 2: return FN<RP, S, 2>(__VA_ARGS__);        \
@@ -1437,7 +1434,7 @@ static int persistent_grid_t(int* grid_out) {
 #define GC_DISPATCH(FN, ...)                                        \
   do {                                                              \
     if (rp64) { GC_DISPATCH_S(int64_t, FN, __VA_ARGS__) }           \
-    else { GC_DISPATCH_S(uint32_t, FN, __VA_ARGS__) }                \
+    else { GC_DISPATCH_S(int32_t, FN, __VA_ARGS__) }                \
   } while (0)
 
 int launch_round(const KArgs& a, bool rp64, int sbytes, int lanes, int phase_id, int round,
@@ -1461,6 +1458,17 @@ int persistent_max_grid(bool rp64, int sbytes, int lanes, int* grid_out) {
 int launch_init(const KArgs& a, void* stream) {
   hipLaunchKernelGGL(k_init, dim3(a.push && a.clear_seen ? 1024 : 64), dim3(kBlock), 0,
                      (hipStream_t)stream, a);
+  return (int)hipGetLastError();
+}
+
+static __global__ void k_widen_rowptr(const int32_t* rowptr, int64_t n, int64_t* out) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i <= n) out[i] = rowptr[i];
+}
+
+int launch_widen_rowptr(const int32_t* rowptr, int64_t n, int64_t* out, void* stream) {
+  hipLaunchKernelGGL(k_widen_rowptr, dim3((unsigned)((n + kBlock) / kBlock)), dim3(kBlock), 0,
+                     (hipStream_t)stream, rowptr, n, out);
   return (int)hipGetLastError();
 }
 

@@ -439,8 +439,8 @@ int launch_flow(const FlowArgs& a, bool rp64, int grid, void* stream) {
   hipLaunchKernelGGL((k_seq_flow<RP_, W_>), dim3(grid), dim3(kBlock), 0, s, a)
   if (rp64 && a.wide) GC_FLOW(int64_t, uint64_t);
   else if (rp64) GC_FLOW(int64_t, uint32_t);
-  else if (a.wide) GC_FLOW(uint32_t, uint64_t);
-  else GC_FLOW(uint32_t, uint32_t);
+  else if (a.wide) GC_FLOW(int32_t, uint64_t);
+  else GC_FLOW(int32_t, uint32_t);
 #undef GC_FLOW
   return (int)hipGetLastError();
 }

@@ -1,5 +1,6 @@
 """GPU: 32-bit row pointers up to their end: 2^31 - 2 CSR entries, so that the
-position behind the last rows' last steps no longer fits 31 bits.  Cliques of 65
+position behind the last rows' last steps no longer fits 31 bits (the library then
+works on a 64-bit copy of them), and the most entries without one.  Cliques of 65
 vertices, single edges, and a clique of 120 vertices whose rows come last: every
 driver and degree class that walks rows, and the check of the CSR.  The expected
 colours, rounds and round sizes are the cliques' closed form (the p-block
@@ -12,9 +13,13 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 K, LAST = 65, 120
-M = 2**31 - 2
-PAIRS = (M - LAST * (LAST - 1)) % (K * (K - 1)) // 2  # single edges that fill up
-Q = (M - LAST * (LAST - 1) - 2 * PAIRS) // (K * (K - 1))
+SIZES = [2**31 - 2, 2**31 - 8194]
+
+
+def _parts(m):
+    # cliques of K, and single edges that fill up
+    pairs = (m - LAST * (LAST - 1)) % (K * (K - 1)) // 2
+    return (m - LAST * (LAST - 1) - 2 * pairs) // (K * (K - 1)), pairs
 
 
 def _clique_rows(k, device):
@@ -22,11 +27,13 @@ def _clique_rows(k, device):
     return torch.stack([torch.cat([j[:i], j[i + 1:]]) for i in range(k)])
 
 
-@pytest.fixture(scope="module")
-def graph():
+@pytest.fixture(scope="module", params=SIZES)
+def graph(request):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     dev = "cuda"
+    M = request.param
+    Q, PAIRS = _parts(M)
     ci = torch.empty(M, dtype=torch.int32, device=dev)
     rows = _clique_rows(K, dev).reshape(1, -1)
     body = ci[:Q * K * (K - 1)].view(Q, K * (K - 1))
@@ -47,10 +54,10 @@ def graph():
                       torch.arange(2, dtype=torch.int32, device=dev).repeat(PAIRS),
                       torch.arange(LAST, dtype=torch.int32, device=dev)])
     yield rp.to(torch.int32), ci, want
-    del ci, body
 
 
-def _sizes():
+def _sizes(m):
+    Q, PAIRS = _parts(m)
     r = np.arange(1, LAST + 1)
     return Q * np.maximum(K + 1 - r, 0) + PAIRS * np.maximum(3 - r, 0) + LAST + 1 - r
 
@@ -77,7 +84,7 @@ def test_cliques_up_to_the_last_entry(graph, name, sorted_rows, options):
             out = G.color()
             assert G.stats() == (LAST, LAST)
             assert torch.equal(out, want)
-            assert np.array_equal(G.round_sizes(), _sizes())
+            assert np.array_equal(G.round_sizes(), _sizes(ci.numel()))
 
 
 @pytest.mark.parametrize("per_block", [128, 400])  # masks, slots
@@ -85,6 +92,7 @@ def test_blocks_up_to_the_last_entry(graph, per_block):
     from paper_1509_08267_amd import gc
     rp, ci, want = graph
     print(f"[case] most entries: blocks of {per_block}", flush=True)
+    Q, PAIRS = _parts(ci.numel())
     with gc.Graph(rp, ci, algorithm="blocks", partitions=want.numel() // per_block) as G:
         out = G.color()
         G.stats()
