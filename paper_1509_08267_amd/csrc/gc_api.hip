@@ -877,17 +877,21 @@ static int color_flow(gc_ctx* h, int32_t* colors_out, int32_t* user_out, hipStre
 }
 
 // Whether calls in the current settings may run rounds in one launch: in the
-// core pass, or all of them in the resident pass.
+// core pass, or all of them in the resident pass.  (Without an edge there is
+// one round: 20,000 vertices 15.5 us by its own pass, 20.2 in one launch.)
 static bool may_fuse_rounds(const gc_ctx* h) {
-  return h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH && h->max_rounds == 0 && !use_seq(h) &&
+  return h->m > 0 && resolve_mode(h) == GC_MODE_GRAPH && h->max_rounds == 0 && !use_seq(h) &&
          h->algorithm != GC_ALGO_BLOCKS && !h->profile && h->wait_polls > 0;
 }
 // The core pass gives up where a vertex finds all its kCoreColors colours taken, which is where
 // the colouring has more of them (a tentative colour never exceeds the final one): with R known,
-// so are the colours.
+// so are the colours.  Before, a graph of such degrees that has two fifths of all possible edges
+// or more is not tried: its first call would run the first 512 rounds twice (complete graph of 600
+// vertices 11.8 ms, by the rounds alone 8.5).
 static bool may_use_core(const gc_ctx* h) {
-  return may_fuse_rounds(h) && !h->core_off &&
-         (h->known_rounds == 0 || h->known_colors <= gc::kCoreColors);
+  if (!may_fuse_rounds(h) || h->core_off) return false;
+  if (h->known_rounds > 0) return h->known_colors <= gc::kCoreColors;
+  return h->maxdeg < gc::kCoreColors || 5.0 * h->m < 2.0 * h->n * (h->n - 1.0);
 }
 static bool use_resident(const gc_ctx* h) {
   return may_fuse_rounds(h) && !h->res_off && gc::resident_fits(h->n, h->m, h->sbytes);
@@ -898,6 +902,14 @@ static bool use_resident(const gc_ctx* h) {
 // the last six rounds by it 197 us a call, by their own passes 182); a round of
 // the passes takes 12 us at least, one of the core 6 to 8.
 constexpr int64_t kCoreMinRounds = 10;
+
+// Whether a small graph runs in the core pass from its first round: not when it is known to take few
+// (a star of 3,000 leaves, two rounds: 45 us by the passes, 97 by the core).  Its first call does in
+// any case: 213 us against 443.
+static bool use_all_core(const gc_ctx* h) {
+  return h->n <= gc::kCoreMax && may_use_core(h) &&
+         (h->known_rounds == 0 || h->known_rounds >= kCoreMinRounds);
+}
 
 // The passes' scratch, allocated once per handle; without room for it the
 // rounds run by their own passes.
@@ -1003,10 +1015,10 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
     return masks ? color_blocks_masks(h, colors_out, user_out, s)
                  : color_blocks(h, colors_out, user_out, s);
   }
-  if (use_seq(h) && h->n > 0 && resolve_mode(h) == GC_MODE_GRAPH && !h->flow_off)
+  if (use_seq(h) && h->m > 0 && resolve_mode(h) == GC_MODE_GRAPH && !h->flow_off)
     return color_flow(h, colors_out, user_out, s);
   const bool resident = use_resident(h) && reserve_resident(h);
-  const bool all_core = !resident && may_use_core(h) && h->n <= gc::kCoreMax && reserve_core(h);
+  const bool all_core = !resident && use_all_core(h) && reserve_core(h);
   if (use_push(h) && !all_core && !resident) {
     if (!h->seen && h->n > 0) {
       const size_t nv = (size_t)(h->n + gc::kWave - 1) / gc::kWave * gc::kWave;  // whole chunks
