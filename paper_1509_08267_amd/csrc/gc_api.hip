@@ -893,8 +893,18 @@ static bool may_use_core(const gc_ctx* h) {
   if (h->known_rounds > 0) return h->known_colors <= gc::kCoreColors;
   return h->maxdeg < gc::kCoreColors || 5.0 * h->m < 2.0 * h->n * (h->n - 1.0);
 }
+// A round of the resident pass reads every vertex's state in every workgroup (5 us at 4,000 vertices,
+// 9 at 24,000, and 2 more with rows of 20 entries), one of the rounds' own passes does not, so that
+// many rounds with little work each are left to those on the larger graphs, once R is known.  us per
+// call, rounds / resident: 20,000 vertices in cliques of 20 190 / 209, of 40 402 / 427, 18,000 in
+// cliques of 60 719 / 734, 150 x 150 grid 1,295 / 1,333; but path of 20,000 84,565 / 78,071, uniform
+// random graphs of 20,000 and degree 4 72 / 67, 24,000 and 12 126 / 119, and unsorted rows, which
+// the rounds read whole, the first three 222 / 209, 508 / 427, 945 / 733.
 static bool use_resident(const gc_ctx* h) {
-  return may_fuse_rounds(h) && !h->res_off && gc::resident_fits(h->n, h->m, h->sbytes);
+  if (!may_fuse_rounds(h) || h->res_off || !gc::resident_fits(h->n, h->m, h->sbytes)) return false;
+  const bool light = h->known_rounds > 8 && h->m < 24000 * h->known_rounds;
+  const bool sparse = h->m < 8 * h->n;
+  return !(light && (sparse ? h->n > 20480 : h->n > 16384 && (h->flags & GC_ROWS_SORTED)));
 }
 
 // Rounds that the core pass has to replace to pay for collecting its vertices
@@ -1123,8 +1133,9 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
       }
     } else {
       const int K = std::max(1, h->chunk_rounds);
-      // rounds of a chunk; the first one is queued without a look at round 1
-      bool look = mode == GC_MODE_HOST || h->max_rounds > 0 || h->n == 0;
+      // rounds of a chunk; the first one is queued without a look at round 1 (which is the only
+      // one without an edge)
+      bool look = mode == GC_MODE_HOST || h->max_rounds > 0 || h->m == 0;
       for (;; look = true) {
         if (look) {
           LCHECK(h, gc::launch_report(a, r, h->fin_dev, s));

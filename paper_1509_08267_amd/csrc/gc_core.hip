@@ -82,7 +82,7 @@ __device__ __forceinline__ bool poll(const uint64_t* p, uint32_t tag, Ctrl* c, i
       *out = x;
       return true;
     }
-    if (++spins > polls)
+    if (++spins >= polls)
       __hip_atomic_store(&c->abort.v, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((spins & 1023) == 0 &&
         __hip_atomic_load(&c->abort.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))

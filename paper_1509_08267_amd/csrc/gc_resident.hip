@@ -73,7 +73,7 @@ __device__ __forceinline__ bool poll_words(const uint64_t* p, const int* i, uint
     for (int k = 0; k < K; ++k)
       if (((want >> k) & 1) && (uint32_t)(x[k] >> 48) == tag) want &= ~(1u << k);
     if (!want) break;
-    if (++spins > polls)
+    if (++spins >= polls)
       __hip_atomic_store(&c->abort.v, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((spins & 1023) == 0 &&
         __hip_atomic_load(&c->abort.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
