@@ -91,11 +91,31 @@ __device__ __forceinline__ int wave_max(int x) {
   return __builtin_amdgcn_readlane(x, kWave - 1);
 }
 
+constexpr int kDeepWords = 8;
+constexpr int kDeepBits = 32 * kDeepWords;
+constexpr int kDeepPitch = kDeepWords + 1;
+
+// First clear bit of a lane's LDS words, -1 for none.
+__device__ __forceinline__ int deep_free(const uint32_t* more) {
+  int c = -1;
+#pragma unroll
+  for (int q = kDeepWords - 1; q >= 0; --q) {
+    const uint32_t x = more[q];
+    if (x != ~0u) c = 32 * q + __builtin_ctz(~x);
+  }
+  return c;
+}
+
 // The vertices s0 .. s0 + cnt - 1 (cnt <= 64), one per lane.  The loop is
 // wave-uniform and every lane keeps its own place in its own row, so no lane
-// waits inside it.  Returns whether to stop (abort).
-template <typename RP, typename W>
-__device__ bool flow_light(const FlowArgs& a, int s0, int cnt) {
+// waits inside it.  Returns whether to stop (abort).  A lane holds the taken
+// colours of a window of 64 and walks its row again for the next one.  Where a lane
+// walks rows of more than 64 entries (DEEP) the window goes on for kDeepBits colours
+// in LDS (deep, this wavefront's own): a second walk took ten times as long as a
+// link of the chain (200 cliques of 200 vertices 7.5 ms, now 0.28; four words in
+// registers cost uniform random graphs of such degrees 10 to 20%).
+template <typename RP, typename W, bool DEEP>
+__device__ bool flow_light(const FlowArgs& a, int s0, int cnt, uint32_t* deep) {
   const RP* __restrict__ rp = (const RP*)a.rowptr;
   W* const word = (W*)a.word;
   const W cmask = ((W)1 << a.cbits) - 1;
@@ -108,6 +128,9 @@ __device__ bool flow_light(const FlowArgs& a, int s0, int cnt) {
   int pend = 0;  // bit j: entry u[j] is not yet final
   int u[kFlow] = {};
   uint64_t m = 0;
+  uint32_t* const more = deep + lane_id() * kDeepPitch;
+  if (DEEP)
+    for (int q = 0; q < kDeepWords; ++q) more[q] = 0;
   int top = 0;  // largest round among the lower neighbours
   long spins = 0;
   while (__ballot(alive)) {
@@ -136,21 +159,29 @@ __device__ bool flow_light(const FlowArgs& a, int s0, int cnt) {
           pend &= ~(1 << j);
           const unsigned rel = (unsigned)(w[j] & cmask) - (unsigned)base;
           if (rel < 64u) m |= 1ull << rel;
+          else if (DEEP && rel < 64u + kDeepBits) more[(rel - 64u) >> 5] |= 1u << (rel & 31);
           top = max(top, (int)(w[j] >> a.cbits));
           moved = true;
         }
       first = false;
     }
     if (alive && !pend) {
+      // (the first window at once: this is the chain's own link)
       if (!past) {
         fetch = true;
       } else if (m != ~0ull) {
         const W x = ((W)(top + 1) << a.cbits) | (W)(base + __builtin_ctzll(~m));
         __hip_atomic_store(&word[v], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         alive = false;
-      } else {  // all of base..base+63 are taken: slide the window
-        base += 64;
+      } else if (const int c = DEEP ? deep_free(more) : -1; c >= 0) {
+        const W x = ((W)(top + 1) << a.cbits) | (W)(base + 64 + c);
+        __hip_atomic_store(&word[v], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        alive = false;
+      } else {  // the whole window is taken: slide it
+        base += 64 + (DEEP ? kDeepBits : 0);
         m = 0;
+        if (DEEP)
+          for (int q = 0; q < kDeepWords; ++q) more[q] = 0;
         k = b;
         fetch = true;
       }
@@ -224,8 +255,9 @@ __device__ bool flow_wave(const FlowArgs& a, int v, RP b, RP e, uint32_t* bm) {
   }
 }
 
-template <typename RP, typename W>
+template <typename RP, typename W, bool DEEP>
 __global__ __launch_bounds__(kBlock) void k_seq_flow(FlowArgs a) {
+  __shared__ uint32_t deep[kWavesPerBlock][DEEP ? kWave * kDeepPitch : 1];
   __shared__ uint32_t bitmap[kWavesPerBlock][kFlowBits / 32];
   const RP* __restrict__ rp = (const RP*)a.rowptr;
   const int units = *a.units;
@@ -239,7 +271,7 @@ __global__ __launch_bounds__(kBlock) void k_seq_flow(FlowArgs a) {
     if (s1 - s0 == 1 && rp[s0 + 1] - rp[s0] > (RP)a.light_max)
       stop = flow_wave<RP, W>(a, s0, rp[s0], rp[s0 + 1], bitmap[threadIdx.x / kWave]);
     else
-      stop = flow_light<RP, W>(a, s0, s1 - s0);
+      stop = flow_light<RP, W, DEEP>(a, s0, s1 - s0, deep[threadIdx.x / kWave]);
     if (stop) break;
   }
 }
@@ -435,12 +467,20 @@ int launch_flow_clear(const FlowArgs& a, int grid, void* stream) {
 
 int launch_flow(const FlowArgs& a, bool rp64, int grid, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-#define GC_FLOW(RP_, W_) \
-  hipLaunchKernelGGL((k_seq_flow<RP_, W_>), dim3(grid), dim3(kBlock), 0, s, a)
-  if (rp64 && a.wide) GC_FLOW(int64_t, uint64_t);
-  else if (rp64) GC_FLOW(int64_t, uint32_t);
-  else if (a.wide) GC_FLOW(int32_t, uint64_t);
-  else GC_FLOW(int32_t, uint32_t);
+#define GC_FLOW(RP_, W_)                                                            \
+  if (a.light_max <= 64)                                                            \
+    hipLaunchKernelGGL((k_seq_flow<RP_, W_, false>), dim3(grid), dim3(kBlock), 0, s, a); \
+  else                                                                              \
+    hipLaunchKernelGGL((k_seq_flow<RP_, W_, true>), dim3(grid), dim3(kBlock), 0, s, a)
+  if (rp64 && a.wide) {
+    GC_FLOW(int64_t, uint64_t);
+  } else if (rp64) {
+    GC_FLOW(int64_t, uint32_t);
+  } else if (a.wide) {
+    GC_FLOW(int32_t, uint64_t);
+  } else {
+    GC_FLOW(int32_t, uint32_t);
+  }
 #undef GC_FLOW
   return (int)hipGetLastError();
 }
