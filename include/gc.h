@@ -159,7 +159,7 @@ enum gc_option {
                                 5 with int64 row pointers)                         */
   GC_OPT_MAX_ROUNDS = 5,     /* stop after this many rounds (0 = no cap); leftover
                                 vertices make gc_get_stats return GC_EROUNDS       */
-  GC_OPT_CHUNK_ROUNDS = 6,   /* rounds queued per read-back in CHUNKED/GRAPH (8)     */
+  GC_OPT_CHUNK_ROUNDS = 6,   /* rounds queued per read-back in CHUNKED/GRAPH (16)    */
   GC_OPT_MEDIUM_DEGREE = 7,  /* deg > this: a wavefront per vertex; 0 = auto         */
   GC_OPT_MAX_DEGREE = 8,     /* (get only) maximum degree of the graph              */
   GC_OPT_MEDIUM_COUNT = 9,   /* (get only) vertices on the wavefront path           */

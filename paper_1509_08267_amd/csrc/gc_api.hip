@@ -150,6 +150,7 @@ struct gc_ctx {
   int wait_polls = 1 << 20;  // polls after which a wait in them gives up (about a second); 0: unused
   enum { kNone, kRes, kCore } fused = kNone;  // the pass that the last call took
 
+  Captured chunk;  // chunk_rounds rounds, of a first call that has seen many
   Captured exact;  // R - 1 rounds, once R is known
 
   // profiling (GC_OPT_PROFILE): events around the kernels of a call
@@ -320,6 +321,7 @@ static void drop(Captured& c) {
 
 static void free_ctx(gc_ctx* h) {
   if (!h) return;
+  drop(h->chunk);
   drop(h->exact);
   for (hipEvent_t& e : h->pev)
     if (e) (void)hipEventDestroy(e);
@@ -926,6 +928,12 @@ static bool use_all_core(const gc_ctx* h) {
          (h->known_rounds == 0 || h->known_rounds >= kCoreMinRounds);
 }
 
+// Rounds that a first call queues by direct launches before it captures a chunk of them: that costs
+// about a millisecond and gives a microsecond per round at most, where the launches are what takes
+// the time.  First calls, ms, direct / captured: path of 100,000 vertices, 50,001 rounds, 522 / 475;
+// 400 x 400 grid, 400 rounds, 4.4 / 5.1, 800 x 800, 800 rounds, 11.6 / 12.3.
+constexpr int kCaptureAfter = 2048;
+
 // The passes' scratch, allocated once per handle; without room for it the
 // rounds run by their own passes.
 static bool reserve_core(gc_ctx* h) {
@@ -1138,6 +1146,7 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
       }
     } else {
       const int K = std::max(1, h->chunk_rounds);
+      int base = 2;  // first round of a captured chunk, as on the device
       // rounds of a chunk; the first one is queued without a look at round 1 (which is the only
       // one without an edge)
       bool look = mode == GC_MODE_HOST || h->max_rounds > 0 || h->m == 0;
@@ -1160,9 +1169,19 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
                                      "converging (internal error)", r, (long long)h->n);
         int upto = mode == GC_MODE_HOST ? r + 1 : r + K;
         if (h->max_rounds > 0) upto = std::min(upto, h->max_rounds);
-        for (int q = r + 1; q <= upto; ++q) {
-          LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 0, q, false, grid, s));
-          LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 1, q, false, grid, s));
+        if (mode == GC_MODE_GRAPH && r > kCaptureAfter) {
+          if (!usable(h->chunk, K, L, grid, a)) {
+            rc = capture(h, h->chunk, a, L, K);
+            if (rc) return rc;
+          }
+          if (base <= r) LCHECK(h, gc::launch_advance_base(a, r + 1 - base, s));
+          HIPCHECK(h, hipGraphLaunch(h->chunk.exec, s));
+          base = upto + 1;
+        } else {
+          for (int q = r + 1; q <= upto; ++q) {
+            LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 0, q, false, grid, s));
+            LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 1, q, false, grid, s));
+          }
         }
         r = upto;
       }
