@@ -933,6 +933,9 @@ static bool use_all_core(const gc_ctx* h) {
 // the time.  First calls, ms, direct / captured: path of 100,000 vertices, 50,001 rounds, 522 / 475;
 // 400 x 400 grid, 400 rounds, 4.4 / 5.1, 800 x 800, 800 rounds, 11.6 / 12.3.
 constexpr int kCaptureAfter = 2048;
+// Rounds of one captured chunk at most: the runtime ends the process on graphs of a few hundred
+// thousand nodes.
+constexpr int kCaptureMost = 16384;
 
 // The passes' scratch, allocated once per handle; without room for it the
 // rounds run by their own passes.
@@ -1129,16 +1132,23 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
       }
       h->timed_rounds = K;
     } else if (mode == GC_MODE_GRAPH && h->known_rounds > 0) {
-      // R is known: queue rounds 2..R, or those before the core pass, in one
-      // captured chunk, no read-back.
+      // R is known: queue rounds 2..R, or those before the core pass, as a captured
+      // chunk, launched again and again if there are very many, no read-back.
       const bool core = h->core_round >= 1 && may_use_core(h) && reserve_core(h);
       const int K = (int)(core ? h->core_round : h->known_rounds) - 1;
       if (K > 0) {
-        if (!usable(h->exact, K, L, grid, a)) {
-          rc = capture(h, h->exact, a, L, K);
+        const int C = std::min(K, kCaptureMost);
+        if (!usable(h->exact, C, L, grid, a)) {
+          rc = capture(h, h->exact, a, L, C);
           if (rc) return rc;
         }
-        HIPCHECK(h, hipGraphLaunch(h->exact.exec, s));
+        int r = 1;
+        for (; r + C <= K + 1; r += C) HIPCHECK(h, hipGraphLaunch(h->exact.exec, s));
+        while (r < K + 1) {
+          ++r;
+          LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 0, r, false, grid, s));
+          LCHECK(h, gc::launch_round(a, h->rp64, h->sbytes, L, 1, r, false, grid, s));
+        }
       }
       if (core) {
         rc = color_core(h, a, (int)h->core_round, h->core_size, &w, s);

@@ -36,3 +36,22 @@ def test_first_calls_with_many_rounds(n, chunk, algorithm):
             assert np.array_equal(out.cpu().numpy(), ref.colors)
             if i == 0:
                 G.set("lanes", 4)  # (the captured chunk no longer fits)
+
+
+@pytest.mark.parametrize("n", [32_766, 32_768, 32_770, 65_600])  # n // 2 + 1 rounds
+def test_known_rounds_beyond_one_chunk(n):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1509_08267_amd import gc
+    print(f"[case] many known rounds {n}", flush=True)
+    g = graphgen.path(n)
+    rp, ci = torch.from_numpy(g.rowptr).cuda(), torch.from_numpy(g.colidx).cuda()
+    want = torch.arange(n, dtype=torch.int32, device="cuda") % 2
+    sizes = n - 2 * np.arange(n // 2 + 1)  # in each round the two lowest ids left (one in the first)
+    sizes[1:] += 1
+    with gc.Graph(rp, ci, wait_polls=0) as G:
+        for _ in range(3):
+            out = G.color()
+            assert G.stats() == (n // 2 + 1, 2)
+            assert torch.equal(out, want)
+            assert np.array_equal(G.round_sizes(), sizes)
