@@ -110,12 +110,14 @@ def host_info():
 
 
 def kernel_source_hash():
-    """Hash of the kernel sources and of the engine that picks their launch
-    shape; a committed counter summary is used only while it matches."""
+    """Hash of the library's sources (every kernel, and the engine that picks
+    their launch shape); a committed counter summary is used only while it matches."""
     h = hashlib.sha256()
-    for f in ("gc_kernels.hip", "gc_batch.hip", "gc_device.h", "gc_internal.h", "gc_api.hip"):
-        with open(os.path.join(ROOT, "paper_1509_08267_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
+    csrc = os.path.join(ROOT, "paper_1509_08267_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        if f.endswith((".hip", ".h")):
+            with open(os.path.join(csrc, f), "rb") as fh:
+                h.update(fh.read())
     return h.hexdigest()[:16]
 
 
