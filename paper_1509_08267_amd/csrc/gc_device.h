@@ -604,27 +604,19 @@ __device__ __forceinline__ bool ready_group(const int32_t* __restrict__ colidx,
   return true;
 }
 
-// Does a lower-id neighbour of v carry tentative colour t?  Group of L lanes.
-// With sorted rows the scan stops at the first neighbour id >= v.
+// Does a lower-id neighbour of v carry tentative colour t?  Group of L lanes; the whole row.
 template <typename RP, typename S, int L>
 __device__ __forceinline__ bool detect_group(const int32_t* __restrict__ colidx,
                                              const S* __restrict__ st, RP b, RP e,
-                                             int v, int t, int gl, uint64_t gmask, bool sorted) {
+                                             int v, int t, int gl, uint64_t gmask) {
   for (RP kb = b; kb < e; kb += L) {
     RP k = kb + gl;
-    bool conf = false, past = false;
+    bool conf = false;
     if (k < e) {
       int u = colidx[k];
-      if (u < v) {
-        conf = tent_of(st[u]) == t;
-      } else {
-        past = true;
-      }
-    } else {
-      past = true;
+      if (u < v) conf = tent_of(st[u]) == t;
     }
     if (__ballot(conf) & gmask) return true;
-    if (sorted && (__ballot(past) & gmask)) return false;
   }
   return false;
 }

@@ -556,7 +556,7 @@ __device__ void medium_phase(const KArgs& a, long wave_gid, long nwaves, Tally& 
           if (lane == 0) a.skip[vv] = sk;
           pb = b + sk;
         } else {
-          lose = detect_group<RP, S, kWave>(a.colidx, st, b, e, vv, t, lane, ~0ull, false);
+          lose = detect_group<RP, S, kWave>(a.colidx, st, b, e, vv, t, lane, ~0ull);
         }
         if (lane == 0) {
           if (!lose) st[vv] = (S)t;
@@ -1172,8 +1172,8 @@ __device__ void color_alone(const KArgs& a, const AloneArgs& w) {
       a.ctrl->last_round.v = r;
     }
     each_open([&](int v, int s) {
-      const bool lose = detect_group<RP, S, kWave>(a.colidx, st, rp[v], rp[v + 1], v, ~s, lane,
-                                                   ~0ull, false);
+      const bool lose =
+          detect_group<RP, S, kWave>(a.colidx, st, rp[v], rp[v + 1], v, ~s, lane, ~0ull);
       if (lane == 0 && !lose) st[v] = (S)~s;
     });
     __syncthreads();
