@@ -36,9 +36,9 @@
 // in their block pick in parallel, the others in turn with their block's
 // colours in registers.  Larger degrees or blocks take the passes with slots.
 // Bound by phase 2's colour gathers (one per entry of every vertex to
-// recolour, 231 M over the 16 rounds of the uniform random graph of 2^24 edges
-// with p = 16,384, at the 270-290 G/s of L2 gathers).  That call: 4.17 ms with
-// slots, 1.37 with masks.
+// recolour, 231 M over the 17 rounds of the uniform random graph of 2^24 edges
+// with p = 16,384, in 1.1 to 1.2 ms: 200 G/s, where gathers from L2 alone reach
+// 270 to 290).  That call: 4.17 ms with slots, 1.37 with masks.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

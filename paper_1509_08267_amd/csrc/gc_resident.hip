@@ -87,7 +87,8 @@ __device__ __forceinline__ void publish(uint64_t* p, uint32_t tag, uint64_t x) {
 }
 
 // Clears the exchange words, and workgroup g checks that the rows of workgroup
-// g of the colouring fit its LDS (core_fail otherwise).
+// g of the colouring fit its LDS (core_fail otherwise; the caller looks at it in
+// the first call of the pass on a graph).
 template <typename RP>
 __global__ __launch_bounds__(kWave) void k_res_prepare(KArgs a, ResArgs r, int lds) {
   const ResLayout lay(a.n, gridDim.x, lds);
