@@ -298,7 +298,7 @@ static int round_grid(const gc_ctx* h) {
   const int64_t blocks = std::max<int64_t>((waves + gc::kWavesPerBlock - 1) / gc::kWavesPerBlock,
                                            h->hcount);
   const int64_t most = h->cus * (int64_t)kOnePass;
-  const bool even = h->m >= 48 * h->n && 10 * h->m >= 9 * h->n * h->maxdeg;
+  const bool even = h->m >= 48 * h->n && h->m >= 0.9 * h->n * h->maxdeg;
   if (h->blocks_per_cu == 0 && even && blocks <= most) return (int)std::max<int64_t>(1, blocks);
   return (int)std::max<int64_t>(1, std::min<int64_t>(grid_of(h), blocks));
 }
