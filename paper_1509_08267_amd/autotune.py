@@ -156,7 +156,7 @@ def current_setting(graph: "gc.Graph") -> dict:
 
 
 def _class_of(graph: "gc.Graph") -> str:
-    algo = "push" if graph.get(gc.GC_OPT_ALGORITHM) == gc.GC_ALGO_PUSH else "pull"
+    algo = {v: k for k, v in gc.ALGORITHMS.items()}[graph.get(gc.GC_OPT_ALGORITHM)]
     return graph_class(graph.n, graph.m, graph.get(gc.GC_OPT_MAX_DEGREE),
                        graph.rowptr.dtype == torch.int64, algo)
 
