@@ -257,9 +257,16 @@ void set_thread_error(const char* msg);
 // cast to int.  `sbytes` is the state width in bytes (1, 2 or 4).
 int launch_init(const KArgs& a, void* stream);
 int launch_round1(const KArgs& a, bool rp64, int sbytes, int lanes, int grid, void* stream);
+// A graph of kernels in the making, each behind the one before (hipGraph_t, hipGraphNode_t).
+struct KernelChain {
+  void* graph;
+  void* last;  // null before the first
+};
+// With a chain the kernels become nodes of its graph and the stream is not used.
 int launch_round(const KArgs& a, bool rp64, int sbytes, int lanes, int phase /*0 spec, 1 detect*/,
-                 int round, bool round_from_base, int grid, void* stream);
-int launch_advance_base(const KArgs& a, int by, void* stream);
+                 int round, bool round_from_base, int grid, void* stream,
+                 KernelChain* chain = nullptr);
+int launch_advance_base(const KArgs& a, int by, void* stream, KernelChain* chain = nullptr);
 // Into pinned memory, after round `round`: out[0] whether vertices are left,
 // out[1] the round's size |U_round|.
 int launch_report(const KArgs& a, int round, int32_t* out, void* stream);

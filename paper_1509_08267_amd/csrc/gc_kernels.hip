@@ -33,6 +33,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstdint>
+#include <tuple>
 
 #include "gc_device.h"
 #include "gc_internal.h"
@@ -1322,22 +1323,40 @@ __global__ __launch_bounds__(kBlock) void k_classify(const RP* rowptr, int32_t n
 
 // ------------------------------------------------------ host launchers --
 
+// Launches kernel(args...), or adds it to a chain.
+template <typename... P, typename... A>
+static int put(void (*kernel)(P...), int grid, int block, hipStream_t s, KernelChain* chain,
+               A... args) {
+  if (!chain) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, s, args...);
+    return (int)hipGetLastError();
+  }
+  std::tuple<P...> values(args...);
+  return std::apply(
+      [&](auto&... v) {
+        void* ptrs[] = {(void*)&v...};
+        hipKernelNodeParams p{};
+        p.func = (void*)kernel;
+        p.gridDim = dim3(grid);
+        p.blockDim = dim3(block);
+        p.kernelParams = ptrs;
+        hipGraphNode_t before = (hipGraphNode_t)chain->last, node = nullptr;
+        const hipError_t e = hipGraphAddKernelNode(&node, (hipGraph_t)chain->graph,
+                                                   before ? &before : nullptr, before ? 1 : 0, &p);
+        if (e == hipSuccess) chain->last = node;
+        return (int)e;
+      },
+      values);
+}
+
 template <typename RP, typename S, int L>
 static int launch_round_t(const KArgs& a, int phase_id, int round, bool from_base, int grid,
-                          hipStream_t s) {
+                          hipStream_t s, KernelChain* chain = nullptr) {
   if (phase_id == kSpec)
-    hipLaunchKernelGGL((k_phase<RP, S, L, kSpec>), dim3(grid), dim3(kBlock), 0, s, a, round,
-                       (int)from_base);
-  else {
-    hipLaunchKernelGGL((k_phase<RP, S, L, kDetect>), dim3(grid), dim3(kBlock), 0, s, a, round,
-                       (int)from_base);
-    if (a.tasks) {
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return (int)e;
-      hipLaunchKernelGGL((k_push_tasks<S>), dim3(grid), dim3(kBlock), 0, s, a);
-    }
-  }
-  return (int)hipGetLastError();
+    return put(k_phase<RP, S, L, kSpec>, grid, kBlock, s, chain, a, round, (int)from_base);
+  const int rc = put(k_phase<RP, S, L, kDetect>, grid, kBlock, s, chain, a, round, (int)from_base);
+  if (rc || !a.tasks) return rc;
+  return put(k_push_tasks<S>, grid, kBlock, s, chain, a);
 }
 
 template <typename RP, typename S, int L>
@@ -1438,8 +1457,9 @@ static int persistent_grid_t(int* grid_out) {
   } while (0)
 
 int launch_round(const KArgs& a, bool rp64, int sbytes, int lanes, int phase_id, int round,
-                 bool round_from_base, int grid, void* stream) {
-  GC_DISPATCH(launch_round_t, a, phase_id, round, round_from_base, grid, (hipStream_t)stream);
+                 bool round_from_base, int grid, void* stream, KernelChain* chain) {
+  GC_DISPATCH(launch_round_t, a, phase_id, round, round_from_base, grid, (hipStream_t)stream,
+              chain);
 }
 
 int launch_round1(const KArgs& a, bool rp64, int sbytes, int lanes, int grid, void* stream) {
@@ -1481,9 +1501,8 @@ int launch_fill_tent0(const KArgs& a, int sbytes, int grid, void* stream) {
   return (int)hipGetLastError();
 }
 
-int launch_advance_base(const KArgs& a, int by, void* stream) {
-  hipLaunchKernelGGL(k_advance_base, dim3(1), dim3(64), 0, (hipStream_t)stream, a.ctrl, by);
-  return (int)hipGetLastError();
+int launch_advance_base(const KArgs& a, int by, void* stream, KernelChain* chain) {
+  return put(k_advance_base, 1, 64, (hipStream_t)stream, chain, a.ctrl, by);
 }
 
 int launch_report(const KArgs& a, int round, int32_t* out, void* stream) {
