@@ -174,8 +174,8 @@ enum gc_option {
   GC_OPT_PROFILE = 13,       /* 1: time the kernels of each call with HIP events
                                 recorded on the call's stream; once R is known
                                 the rounds are launched directly (not as a
-                                captured graph) with an event around every
-                                kernel; read with gc_get_profile           */
+                                graph) with an event around every kernel;
+                                read with gc_get_profile                   */
   GC_OPT_ALGORITHM = 14,     /* enum gc_algorithm (default GC_ALGO_AUTO)           */
   GC_OPT_PARTITIONS = 15,    /* p for GC_ALGO_BLOCKS; 0 = auto (64 per compute unit) */
   GC_OPT_ORDER = 16,         /* enum gc_order (default GC_ORDER_NATURAL)            */
@@ -245,7 +245,7 @@ enum gc_mode {
   GC_MODE_HOST = 1,       /* one round per host iteration, a flag read back       */
   GC_MODE_CHUNKED = 2,    /* rounds queued in chunks; empty rounds exit at once   */
   GC_MODE_PERSISTENT = 3, /* one cooperative kernel, device-side round loop      */
-  GC_MODE_GRAPH = 4       /* a captured hipGraph of a chunk of rounds            */
+  GC_MODE_GRAPH = 4       /* a hipGraph of a chunk of rounds                     */
 };
 int gc_set_option(gc_handle h, int option, int64_t value);
 int gc_get_option(gc_handle h, int option, int64_t *value);

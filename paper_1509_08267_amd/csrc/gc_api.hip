@@ -5,7 +5,7 @@
 //   GRAPH       (default) the first call on a handle queues rounds in chunks and
 //               learns the round count R from one look at the stream per
 //               chunk; because R is a function of the (unchanged) graph alone,
-//               later calls queue exactly the rounds it takes, as a captured
+//               later calls queue exactly the rounds it takes, as a
 //               hipGraph (speculate + detect launches with a device-side round
 //               base), and never wait on the host.  Small graphs, the last
 //               rounds of larger ones and sequential First Fit run several
@@ -49,10 +49,10 @@ struct Pinned {  // read-back area in pinned host memory
 };
 
 // One instantiated chunk of K rounds.  The graph holds the kernel arguments
-// and grid of its capture, so it is replayed only while everything the round
+// and grid it was built with, so it is replayed only while everything the round
 // kernels read from them is unchanged (options and reallocations change the
 // degree lists, the flag blocks and the grid).
-struct Captured {
+struct RoundGraph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   int k = 0, lanes = 0, grid = 0;
@@ -150,8 +150,8 @@ struct gc_ctx {
   int wait_polls = 1 << 20;  // polls after which a wait in them gives up (about a second); 0: unused
   enum { kNone, kRes, kCore } fused = kNone;  // the pass that the last call took
 
-  Captured chunk;  // chunk_rounds rounds, of a first call that has seen many
-  Captured exact;  // R - 1 rounds, once R is known
+  RoundGraph chunk;  // chunk_rounds rounds, of a first call that has seen many
+  RoundGraph exact;  // R - 1 rounds, once R is known
 
   // profiling (GC_OPT_PROFILE): events around the kernels of a call
   bool profile = false;
@@ -330,10 +330,10 @@ static int classify(gc_ctx* h, hipStream_t s) {
   return GC_OK;
 }
 
-static void drop(Captured& c) {
+static void drop(RoundGraph& c) {
   if (c.exec) (void)hipGraphExecDestroy(c.exec);
   if (c.graph) (void)hipGraphDestroy(c.graph);
-  c = Captured();
+  c = RoundGraph();
 }
 
 static void free_ctx(gc_ctx* h) {
@@ -482,63 +482,47 @@ static int ensure_idle(gc_ctx* h) {
 
 static int resolve_mode(const gc_ctx* h) {
   int mode = h->mode == GC_MODE_AUTO ? GC_MODE_GRAPH : h->mode;
-  // a captured chunk cannot stop inside itself: honour a round cap by queueing
+  // a chunk's graph cannot stop inside itself: honour a round cap by queueing
   if (mode == GC_MODE_GRAPH && h->max_rounds > 0) mode = GC_MODE_CHUNKED;
   return mode;
 }
 
 // K rounds (speculate + detect, rounds relative to the device-side round base)
-// and the base advance, queued on `cs` or added to a chain.
-static int queue_chunk(gc_ctx* h, const KArgs& a, int L, int K, hipStream_t cs,
-                       gc::KernelChain* chain) {
+// and the base advance as a graph in c.  The kernels are added as nodes, not
+// captured from a stream: while a stream captures, another thread's wait for the
+// whole device is refused, ends the capture and has faulted in the runtime on
+// the capturing stream.  Replays, us, captured / nodes: uniform
+// random graph of 2^24 edges 785.7 / 785.4, 2,700,011 unsorted edges 275 / 277,
+// 4,000,000 edges on 8,000 vertices 2,703 / 2,714.
+static int build_graph(gc_ctx* h, RoundGraph& c, const KArgs& a, int L, int K) {
+  drop(c);
   const int grid = round_grid(h);
+  HIPCHECK(h, hipGraphCreate(&c.graph, 0));
+  gc::KernelChain chain{c.graph, nullptr};
   int rc = 0;
   for (int j = 0; j < K && !rc; ++j) {
-    rc = gc::launch_round(a, h->rp64, h->sbytes, L, 0, j, true, grid, cs, chain);
-    if (!rc) rc = gc::launch_round(a, h->rp64, h->sbytes, L, 1, j, true, grid, cs, chain);
+    rc = gc::launch_round(a, h->rp64, h->sbytes, L, 0, j, true, grid, nullptr, &chain);
+    if (!rc) rc = gc::launch_round(a, h->rp64, h->sbytes, L, 1, j, true, grid, nullptr, &chain);
   }
-  return rc ? rc : gc::launch_advance_base(a, K, cs, chain);
-}
-
-// Those as a graph in c.  Captured from a stream where that works; it fails
-// when another thread waits for the whole device meanwhile, and the nodes are
-// then added one by one (whose replays take a sixth of a microsecond more per
-// kernel: uniform random graph of 2^24 edges 781 -> 789 us).
-static int capture(gc_ctx* h, Captured& c, const KArgs& a, int L, int K) {
-  drop(c);
-  hipStream_t cs;
-  HIPCHECK(h, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-  int rc = (int)hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-  if (!rc) {
-    rc = queue_chunk(h, a, L, K, cs, nullptr);
-    const hipError_t e = hipStreamEndCapture(cs, &c.graph);
-    if (!rc) rc = (int)e;
-  }
-  (void)hipStreamDestroy(cs);
-  if (rc) {
-    (void)hipGetLastError();
-    drop(c);
-    HIPCHECK(h, hipGraphCreate(&c.graph, 0));
-    gc::KernelChain chain{c.graph, nullptr};
-    rc = queue_chunk(h, a, L, K, nullptr, &chain);
-  }
+  if (!rc) rc = gc::launch_advance_base(a, K, nullptr, &chain);
   if (!rc) rc = (int)hipGraphInstantiate(&c.exec, c.graph, nullptr, nullptr, 0);
   if (rc) {
+    (void)hipGetLastError();
     c.exec = nullptr;
     drop(c);
     return set_err(h, GC_EDEVICE, "graph of rounds: %s", hipGetErrorString((hipError_t)rc));
   }
   c.k = K;
   c.lanes = L;
-  c.grid = round_grid(h);
+  c.grid = grid;
   c.args = a;
   return GC_OK;
 }
 
-// Fields of KArgs that the captured round kernels read (the call's epoch and
+// Fields of KArgs that the graph's round kernels read (the call's epoch and
 // output pointer reach them through the control block and the finish kernel,
 // which are launched outside the graph).
-static bool usable(const Captured& c, int K, int L, int grid, const KArgs& a) {
+static bool usable(const RoundGraph& c, int K, int L, int grid, const KArgs& a) {
   const KArgs& b = c.args;
   return c.exec && c.k == K && c.lanes == L && c.grid == grid && b.rowptr == a.rowptr &&
          b.colidx == a.colidx && b.st == a.st && b.n == a.n && b.light_max == a.light_max &&
@@ -951,14 +935,14 @@ static bool use_all_core(const gc_ctx* h) {
          (h->known_rounds == 0 || h->known_rounds >= kCoreMinRounds);
 }
 
-// Rounds that a first call queues by direct launches before it captures a chunk of them: that costs
+// Rounds that a first call queues by direct launches before it makes a graph of a chunk of them: that costs
 // about a millisecond and gives a microsecond per round at most, where the launches are what takes
-// the time.  First calls, ms, direct / captured: path of 100,000 vertices, 50,001 rounds, 522 / 475;
+// the time.  First calls, ms, direct / graph: path of 100,000 vertices, 50,001 rounds, 522 / 475;
 // 400 x 400 grid, 400 rounds, 4.4 / 5.1, 800 x 800, 800 rounds, 11.6 / 12.3.
-constexpr int kCaptureAfter = 2048;
-// Rounds of one captured chunk at most: the runtime ends the process on graphs of a few hundred
+constexpr int kGraphAfter = 2048;
+// Rounds of one graph at most: the runtime ends the process on graphs of a few hundred
 // thousand nodes.
-constexpr int kCaptureMost = 16384;
+constexpr int kGraphMost = 16384;
 
 // The passes' scratch, allocated once per handle; without room for it the
 // rounds run by their own passes.
@@ -1155,14 +1139,14 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
       }
       h->timed_rounds = K;
     } else if (mode == GC_MODE_GRAPH && h->known_rounds > 0) {
-      // R is known: queue rounds 2..R, or those before the core pass, as a captured
-      // chunk, launched again and again if there are very many, no read-back.
+      // R is known: queue rounds 2..R, or those before the core pass, as a graph
+      // of a chunk, launched again and again if there are very many, no read-back.
       const bool core = h->core_round >= 1 && may_use_core(h) && reserve_core(h);
       const int K = (int)(core ? h->core_round : h->known_rounds) - 1;
       if (K > 0) {
-        const int C = std::min(K, kCaptureMost);
+        const int C = std::min(K, kGraphMost);
         if (!usable(h->exact, C, L, grid, a)) {
-          rc = capture(h, h->exact, a, L, C);
+          rc = build_graph(h, h->exact, a, L, C);
           if (rc) return rc;
         }
         int r = 1;
@@ -1179,7 +1163,7 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
       }
     } else {
       const int K = std::max(1, h->chunk_rounds);
-      int base = 2;  // first round of a captured chunk, as on the device
+      int base = 2;  // first round of a graph's chunk, as on the device
       // rounds of a chunk; the first one is queued without a look at round 1 (which is the only
       // one without an edge)
       bool look = mode == GC_MODE_HOST || h->max_rounds > 0 || h->m == 0;
@@ -1202,9 +1186,9 @@ extern "C" int gc_color(gc_handle h, int32_t* colors_out, void* stream) {
                                      "converging (internal error)", r, (long long)h->n);
         int upto = mode == GC_MODE_HOST ? r + 1 : r + K;
         if (h->max_rounds > 0) upto = std::min(upto, h->max_rounds);
-        if (mode == GC_MODE_GRAPH && r > kCaptureAfter) {
+        if (mode == GC_MODE_GRAPH && r > kGraphAfter) {
           if (!usable(h->chunk, K, L, grid, a)) {
-            rc = capture(h, h->chunk, a, L, K);
+            rc = build_graph(h, h->chunk, a, L, K);
             if (rc) return rc;
           }
           if (base <= r) LCHECK(h, gc::launch_advance_base(a, r + 1 - base, s));

@@ -56,7 +56,7 @@ struct Ctrl {
   Line more[3];          // slot r % 3 == 1 when round r has uncoloured vertices
   ClassLine cls[3];      // slot r % 3: the classes with uncoloured vertices in round r
   Line last_round;       // last round that had uncoloured vertices
-  Line round_base;       // first round of the next captured chunk
+  Line round_base;       // first round of the next graph of a chunk
   Line bar;              // grid barrier arrivals (monotonic within a launch)
   Line abort;            // set when a wait for other workgroups exceeded its limit
   Line left;             // vertices still uncoloured after the last round

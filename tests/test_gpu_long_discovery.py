@@ -1,5 +1,5 @@
-"""GPU: first calls with so many rounds that they go on by captured chunks (from
-2,048 rounds on): the last direct chunk, the first and second captured ones, a chunk
+"""GPU: first calls with so many rounds that they go on by graphs of chunks (from
+2,048 rounds on): the last direct chunk, the first and second graphs, a chunk
 size that does not divide, and a call in another mode on the same handle between two
 that search for the round count.  Exact equality with the oracle."""
 import numpy as np
@@ -35,7 +35,7 @@ def test_first_calls_with_many_rounds(n, chunk, algorithm):
                 assert np.array_equal(G.round_sizes(), sizes)
             assert np.array_equal(out.cpu().numpy(), ref.colors)
             if i == 0:
-                G.set("lanes", 4)  # (the captured chunk no longer fits)
+                G.set("lanes", 4)  # (the graph no longer fits)
 
 
 @pytest.mark.parametrize("n", [32_766, 32_768, 32_770, 65_600])  # n // 2 + 1 rounds

@@ -1,5 +1,5 @@
-"""GPU: calls that capture their rounds in two threads while others wait for the whole
-device, which ends a capture: the calls give their result all the same."""
+"""GPU: calls that make graphs of their rounds in two threads while others wait for the
+whole device: the calls give their results, and no wait is refused."""
 import threading
 import time
 
@@ -46,8 +46,9 @@ def test_graphs_of_rounds_beside_device_waits():
         while time.monotonic() < end:
             try:
                 torch.cuda.synchronize()
-            except RuntimeError:  # (HIP refuses the wait while a stream captures)
-                pass
+            except BaseException as e:  # noqa: BLE001
+                failed.append(repr(e))
+                return
             time.sleep(0.0002)
 
     threads = [threading.Thread(target=color, args=(i,)) for i in (0, 1)]
